@@ -2291,104 +2291,4 @@ struct BatchEntry {
     long long steps_left; // at tick start
 };
 
-// ------------------------------------------------------------- reductions
-
-template <class S>
-__global__ __launch_bounds__(256) void reduce_partial(const void* f, int nx, int ny, int nz,
-                                                      int pitch, long long plane, double* part) {
-    double s = 0.0, q = 0.0;
-    const long long rows = (long long)ny * nz;
-    for (long long row = blockIdx.x; row < rows; row += gridDim.x) {
-        const long long base = (row / ny) * plane + (row % ny) * (long long)pitch;
-        for (int x = threadIdx.x; x < nx; x += 256) {
-            const double v = load1<S>(f, base + x);
-            s += v;
-            q += v * v;
-        }
-    }
-    __shared__ double ss[256], sq[256];
-    ss[threadIdx.x] = s;
-    sq[threadIdx.x] = q;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) {
-            ss[threadIdx.x] += ss[threadIdx.x + k];
-            sq[threadIdx.x] += sq[threadIdx.x + k];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = ss[0];
-        part[2 * blockIdx.x + 1] = sq[0];
-    }
-}
-
-#ifdef RD_DEFINE_ENGINE_KERNELS   // non-template kernels: one definition, in the engine
-__global__ __launch_bounds__(256) void reduce_final(const double* part, int n, double h3, double* out) {
-    double s = 0.0, q = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        s += part[2 * i];
-        q += part[2 * i + 1];
-    }
-    __shared__ double ss[256], sq[256];
-    ss[threadIdx.x] = s;
-    sq[threadIdx.x] = q;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) {
-            ss[threadIdx.x] += ss[threadIdx.x + k];
-            sq[threadIdx.x] += sq[threadIdx.x + k];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = ss[0] * h3;
-        out[1] = sq[0] * h3;
-    }
-}
-
-#endif
-
-// ------------------------------------------------------ layout conversion
-
-// dense [nz][ny][nx] of transfer type Src -> padded storage S
-template <class S, class Src>
-__global__ __launch_bounds__(256) void pack_kernel(const void* src, void* dst, int nx, int ny, int nz,
-                                                   int pitch, long long plane) {
-    const long long n = (long long)nx * ny * nz;
-    for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const long long x = i % nx, r = i / nx;
-        const long long y = r % ny, z = r / ny;
-        const float v = Src::up(static_cast<const typename Src::T*>(src)[i]);
-        static_cast<typename S::T*>(dst)[z * plane + y * pitch + x] = S::down(v);
-    }
-}
-
-template <class S, typename DstT>
-__global__ __launch_bounds__(256) void unpack_kernel(const void* src, DstT* dst, int nx, int ny, int nz,
-                                                     int pitch, long long plane) {
-    const long long n = (long long)nx * ny * nz;
-    for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-        const long long x = i % nx, r = i / nx;
-        const long long y = r % ny, z = r / ny;
-        dst[i] = DstT(S::up(static_cast<const typename S::T*>(src)[z * plane + y * pitch + x]));
-    }
-}
-
-#ifdef RD_DEFINE_ENGINE_KERNELS
-// ----------------------------------------------------------- copy ceiling
-
-// One 16-byte element per thread, streamed with non-temporal load/store:
-// the read+write bandwidth ceiling a kernel can reach.
-__global__ __launch_bounds__(256) void copy_kernel(const float4* __restrict__ src,
-                                                   float4* __restrict__ dst, long long n4) {
-    typedef float v4f __attribute__((ext_vector_type(4)));
-    const long long i = blockIdx.x * 256LL + threadIdx.x;
-    if (i < n4) {
-        const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(src) + i);
-        __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(dst) + i);
-    }
-}
-#endif
-
 }  // namespace rdk

@@ -14,11 +14,11 @@
 #include <vector>
 
 #include "rd.h"
-#define RD_DEFINE_ENGINE_KERNELS
 #include "rd_fch_cfg.hpp"
 #include "rd_tring_cfg.hpp"
 #include "rd_batch_cfg.hpp"
 #include "rd_internal.hpp"
+#include "rd_io.hpp"
 
 using namespace rdk;
 
@@ -79,6 +79,28 @@ PassGroups pass_groups(int model, int ns) {
     default: break;
     }
     return p;
+}
+
+// Workgroups of the layout conversions: runs of whole rows, 4096 cells each
+// (four units of four cells per thread), fewer where that would not give each
+// CU several workgroups.
+struct RowRuns { long long rows; int run; unsigned blocks; bool deep; };
+RowRuns row_runs(int64_t nx, int64_t rows) {
+    const int64_t cells = std::min<int64_t>(IO_DEPTH * IO_CELLS, std::max<int64_t>(IO_CELLS, nx * rows / 2048));
+    // (longer runs where the count of workgroups would not fit a launch)
+    const int64_t row = (nx + 3) / 4 * 4;
+    const int64_t run = std::max<int64_t>({1, cells / row, (rows + 0x3fffffff) / 0x40000000});
+    return RowRuns{(long long)rows, int(run), unsigned((rows + run - 1) / run), run * row > IO_CELLS};
+}
+
+void launch_reduce_partial(int storage, const void* f, int nx, long long rows, int pitch, double* part, int blocks,
+                           hipStream_t s) {
+    const dim3 grid(blocks), block(256);
+    switch (storage) {
+    case RD_F32: hipLaunchKernelGGL((reduce_partial<StF32>), grid, block, 0, s, f, nx, rows, pitch, part); break;
+    case RD_BF16: hipLaunchKernelGGL((reduce_partial<StBF16>), grid, block, 0, s, f, nx, rows, pitch, part); break;
+    default: hipLaunchKernelGGL((reduce_partial<StF16>), grid, block, 0, s, f, nx, rows, pitch, part); break;
+    }
 }
 
 // compute units of the current device (the first query is cached; the
@@ -1177,10 +1199,13 @@ extern "C" int rd_write_field(rd_grid* g, int32_t species, const void* src, int3
         dsrc = stage;
     }
     void* dst = g->buf[g->cur][species];
-    const unsigned blocks = unsigned(std::min<size_t>((n + 255) / 256, 8192));
-    const int nx = int(g->nx), ny = int(g->ny), nz = int(g->nz);
-#define RD_PACK(S, SRC) hipLaunchKernelGGL((pack_kernel<S, SRC>), dim3(blocks), dim3(256), 0, g->stream, \
-                                           dsrc, dst, nx, ny, nz, g->pitch, g->plane)
+    const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
+#define RD_PACK_D(S, SRC, D)                                                                               \
+    hipLaunchKernelGGL((pack_kernel<S, SRC, D>), dim3(rr.blocks), dim3(256), 0, g->stream, dsrc, dst, int(g->nx), \
+                       rr.rows, rr.run, g->pitch)
+#define RD_PACK(S, SRC)                            \
+    if (rr.deep) RD_PACK_D(S, SRC, IO_DEPTH);      \
+    else RD_PACK_D(S, SRC, 1)
 #define RD_PACK_SRC(S)                                   \
     switch (src_dtype) {                                 \
     case RD_F32: RD_PACK(S, StF32); break;               \
@@ -1195,6 +1220,7 @@ extern "C" int rd_write_field(rd_grid* g, int32_t species, const void* src, int3
     }
 #undef RD_PACK_SRC
 #undef RD_PACK
+#undef RD_PACK_D
     const hipError_t e1 = hipGetLastError();
     if (enqueue_only) {
         if (e1 != hipSuccess) return fail(RD_EDEVICE, std::string("pack: ") + hipGetErrorString(e1));
@@ -1223,21 +1249,25 @@ extern "C" int rd_read_field(rd_grid* g, int32_t species, void* dst, int32_t dst
         ddst = stage;
     }
     const void* src = g->buf[g->cur][species];
-    const unsigned blocks = unsigned(std::min<size_t>((n + 255) / 256, 8192));
-    const int nx = int(g->nx), ny = int(g->ny), nz = int(g->nz);
-#define RD_UNPACK(S)                                                                                    \
-    if (dst_dtype == RD_F64)                                                                            \
-        hipLaunchKernelGGL((unpack_kernel<S, double>), dim3(blocks), dim3(256), 0, g->stream, src,       \
-                           static_cast<double*>(ddst), nx, ny, nz, g->pitch, g->plane);                 \
-    else                                                                                                \
-        hipLaunchKernelGGL((unpack_kernel<S, float>), dim3(blocks), dim3(256), 0, g->stream, src,        \
-                           static_cast<float*>(ddst), nx, ny, nz, g->pitch, g->plane);
+    const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
+#define RD_UNPACK_D(S, T, D)                                                                                 \
+    hipLaunchKernelGGL((unpack_kernel<S, T, D>), dim3(rr.blocks), dim3(256), 0, g->stream, src, static_cast<T*>(ddst), \
+                       int(g->nx), rr.rows, rr.run, g->pitch)
+#define RD_UNPACK(S)                                        \
+    if (dst_dtype == RD_F64) {                              \
+        if (rr.deep) RD_UNPACK_D(S, double, IO_DEPTH);      \
+        else RD_UNPACK_D(S, double, 1);                     \
+    } else {                                                \
+        if (rr.deep) RD_UNPACK_D(S, float, IO_DEPTH);       \
+        else RD_UNPACK_D(S, float, 1);                      \
+    }
     switch (g->storage) {
     case RD_F32: RD_UNPACK(StF32) break;
     case RD_BF16: RD_UNPACK(StBF16) break;
     default: RD_UNPACK(StF16) break;
     }
 #undef RD_UNPACK
+#undef RD_UNPACK_D
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
     if (e == hipSuccess && stage) e = hipMemcpy(dst, stage, n * es, hipMemcpyDeviceToHost);
@@ -1266,21 +1296,7 @@ extern "C" int rd_reduce(rd_grid* g, int32_t species, double out[2]) {
     const long long rows = g->ny * g->nz;
     const int blocks = int(std::min<long long>(rows, kRedBlocks));
     const void* f = g->buf[g->cur][species];
-    const int nx = int(g->nx), ny = int(g->ny), nz = int(g->nz);
-    switch (g->storage) {
-    case RD_F32:
-        hipLaunchKernelGGL((reduce_partial<StF32>), dim3(blocks), dim3(256), 0, g->stream, f, nx, ny, nz,
-                           g->pitch, g->plane, g->d_part);
-        break;
-    case RD_BF16:
-        hipLaunchKernelGGL((reduce_partial<StBF16>), dim3(blocks), dim3(256), 0, g->stream, f, nx, ny, nz,
-                           g->pitch, g->plane, g->d_part);
-        break;
-    default:
-        hipLaunchKernelGGL((reduce_partial<StF16>), dim3(blocks), dim3(256), 0, g->stream, f, nx, ny, nz,
-                           g->pitch, g->plane, g->d_part);
-        break;
-    }
+    launch_reduce_partial(g->storage, f, int(g->nx), rows, g->pitch, g->d_part, blocks, g->stream);
     const double h3 = g->h * g->h * g->h;
     hipLaunchKernelGGL(reduce_final, dim3(1), dim3(256), 0, g->stream, g->d_part, blocks, h3, g->d_red);
     RD_HIP(hipGetLastError());
@@ -1302,9 +1318,9 @@ extern "C" int rd_chemical_potential(rd_grid* g, float* dst_host) {
     const size_t n = size_t(g->nx) * g->ny * g->nz;
     float* stage = nullptr;
     RD_HIP(hipMalloc(&stage, n * sizeof(float)));
-    const unsigned blocks = unsigned(std::min<size_t>((n + 255) / 256, 8192));
-    hipLaunchKernelGGL((unpack_kernel<StF32, float>), dim3(blocks), dim3(256), 0, g->stream, g->aux, stage,
-                       int(g->nx), int(g->ny), int(g->nz), g->pitch, g->plane);
+    const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
+    hipLaunchKernelGGL((unpack_kernel<StF32, float, IO_DEPTH>), dim3(rr.blocks), dim3(256), 0, g->stream, g->aux, stage,
+                       int(g->nx), rr.rows, rr.run, g->pitch);
     hipError_t e2 = hipGetLastError();
     if (e2 == hipSuccess) e2 = hipStreamSynchronize(g->stream);
     if (e2 == hipSuccess) e2 = hipMemcpy(dst_host, stage, n * sizeof(float), hipMemcpyDeviceToHost);
@@ -1364,20 +1380,7 @@ extern "C" int rd_reduce_noalloc(const void* field, int32_t dtype, int64_t nx, i
     // partial pair the first kernel writes, so nothing needs clearing
     const long long rows = ny * nz;
     const int blocks = int(std::min<long long>(rows, kRedBlocks));
-    const int ix = int(nx), iy = int(ny), iz = int(nz);
-    const long long plane = nx * ny;
-    switch (dtype) {
-    case RD_F32:
-        hipLaunchKernelGGL((reduce_partial<StF32>), dim3(blocks), dim3(256), 0, st, field, ix, iy, iz, ix, plane, part);
-        break;
-    case RD_BF16:
-        hipLaunchKernelGGL((reduce_partial<StBF16>), dim3(blocks), dim3(256), 0, st, field, ix, iy, iz, ix, plane,
-                           part);
-        break;
-    default:
-        hipLaunchKernelGGL((reduce_partial<StF16>), dim3(blocks), dim3(256), 0, st, field, ix, iy, iz, ix, plane, part);
-        break;
-    }
+    launch_reduce_partial(dtype, field, int(nx), rows, int(nx), part, blocks, st);
     hipLaunchKernelGGL(reduce_final, dim3(1), dim3(256), 0, st, part, blocks, h * h * h, out_dev);
     RD_HIP(hipGetLastError());
     return RD_OK;
