@@ -190,11 +190,17 @@ enum {
                               Laplacian passes of section 4.1 fused).  128-cell
                               x tiles, any nx (a periodic x axis of C needs
                               nx <= 128 or a multiple of 128)                  */
-    RD_KERNEL_TRING = 7    /* FP32 or BF16, 7-point diffusion of one or two
+    RD_KERNEL_TRING = 7,   /* FP32 or BF16, 7-point diffusion of one or two
                               species, Brusselator and the pollutant's passes
                               of one or two species: z-march over
                               128-cell x tiles of ry rows, every field streamed
                               into an LDS ring by one loading wave, any nx     */
+    RD_KERNEL_MARCH = 8    /* FP32 or BF16, forward Euler, rounding to nearest,
+                              7-point diffusion of one species, Brusselator and
+                              pollutant whose fields share their face rules
+                              (mirror or periodic; fixed ghosts along x only):
+                              z-march with the planes in registers, several time
+                              steps per launch                                 */
 };
 typedef struct rd_plan {
     int32_t kernel;       /* RD_KERNEL_*                                        */
@@ -202,21 +208,26 @@ typedef struct rd_plan {
                              LDS: 4 (rows of <= 256 cells) or 8 (257..512);
                              LDS2: 4 (rows of 256 cells) or 8 (of 512);
                              FUSED: waves computing the chemical potential;
+                             MARCH: 4 (cells per lane);
                              TRING: 2 (cells per lane)                         */
     int32_t ry;           /* TILED/BLOCK: rows per wave (1, 2 or 4);
-                             LDS/LDS2/FUSED/TRING: rows per workgroup          */
+                             LDS/LDS2/FUSED/TRING: rows per workgroup;
+                             MARCH: rows per lane (1 or 2)                     */
     int32_t waves;        /* TILED/BLOCK: waves per workgroup (1 or 4);
                              LDS/LDS2: computing waves (plus one loading wave);
                              FUSED: waves updating the fields (plus vx waves
                              for the chemical potential and one loading wave);
                              TRING: computing waves (plus one loading wave, or
                              two when the fields' ring rows times prefetch-3
-                             exceed 63 loads)                                  */
-    int32_t cz;           /* TILED/LDS/LDS2/FUSED/TRING: z planes per workgroup, 0 = all;
+                             exceed 63 loads);
+                             MARCH: waves per workgroup                        */
+    int32_t cz;           /* TILED/LDS/LDS2/FUSED/TRING/MARCH: z planes per workgroup, 0 = all;
                              BLOCK: planes per slab (2, 4 or 8)                */
     int32_t prefetch;     /* TILED: planes in flight ahead of the z window (1-2);
-                             LDS/LDS2/FUSED/TRING: input ring slots            */
-    int32_t order;        /* BLOCK/LDS/LDS2/FUSED/TRING: tile enumeration, 0 = x, then y, then z chunk;
+                             LDS/LDS2/FUSED/TRING: input ring slots;
+                             MARCH: time steps per launch (2 to 4; the rest of a
+                             count in launches of two and one)                 */
+    int32_t order;        /* BLOCK/LDS/LDS2/FUSED/TRING/MARCH: tile enumeration, 0 = x, then y, then z chunk;
                              1 = z chunk fastest (z-neighbour slabs run together
                              on one XCD and share its L2)                       */
     int32_t graph_chunk;  /* rd_step replays hipGraphs of this many steps (even,

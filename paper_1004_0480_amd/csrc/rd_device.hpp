@@ -60,6 +60,7 @@ struct StepArgs {
     int s19;                      // 19-point Laplacian: kx = ky = kz = K/(6h^2)
     int tiles_x, tiles_y, chunks_z, cz;   // tiled decomposition
     int zfast;                    // slab enumeration: z chunk fastest
+    int mg[6];                    // geometry of the multi-step kernels (rd_march_cfg.hpp: MG_*)
     // time-dependent wind (atmospheric model): u_z(t) = wamp sin(t / wper)
     // (wamp when wper = 0), t = t0 + n dt64
     const StepClock* clk_in;      // clock of this step's input state
@@ -369,10 +370,12 @@ struct Nb { float c, xm, xp, ym, yp, zm, zp; };
 
 // sum_d K_d (c[+e_d] + c[-e_d] - 2c), K already divided by h^2
 __device__ __forceinline__ float lap7(const Nb& n, float kx, float ky, float kz) {
-    const float c2 = n.c + n.c;
-    const float dx = (n.xm + n.xp) - c2;
-    const float dy = (n.ym + n.yp) - c2;
-    const float dz = (n.zm + n.zp) - c2;
+    // -2c is exact, so each fma is the sum less twice the centre rounded once,
+    // as a separate doubling and subtraction would give it, in one operation
+    // less
+    const float dx = __fmaf_rn(-2.f, n.c, n.xm + n.xp);
+    const float dy = __fmaf_rn(-2.f, n.c, n.ym + n.yp);
+    const float dz = __fmaf_rn(-2.f, n.c, n.zm + n.zp);
     return __fmaf_rn(kx, dx, __fmaf_rn(ky, dy, kz * dz));
 }
 

@@ -17,6 +17,7 @@
 #include "rd_fch_cfg.hpp"
 #include "rd_tring_cfg.hpp"
 #include "rd_batch_cfg.hpp"
+#include "rd_march_cfg.hpp"
 #include "rd_internal.hpp"
 #include "rd_io.hpp"
 
@@ -156,6 +157,29 @@ hipError_t launch_fch(int storage, int cfg, const StepArgs&, const StepArgs* d, 
     }
 }
 
+hipError_t launch_march(int storage, int pm, int cfg, int k, int variant, const StepArgs* d, long long blocks,
+                        hipStream_t s) {
+    const bool f32 = storage == ST_F32;
+    if (!f32 && storage != ST_BF16) return hipErrorNotSupported;
+    switch (pm) {
+    case PM_DIFF1:
+        return f32 ? launch_march_f32_diff(pm, cfg, k, variant, d, blocks, s)
+                   : launch_march_bf16_diff(pm, cfg, k, variant, d, blocks, s);
+    case PM_BRUSS:
+        return f32 ? launch_march_f32_react(pm, cfg, k, variant, d, blocks, s)
+                   : launch_march_bf16_react(pm, cfg, k, variant, d, blocks, s);
+    default:
+        return f32 ? launch_march_f32_poll(pm, cfg, k, variant, d, blocks, s)
+                   : launch_march_bf16_poll(pm, cfg, k, variant, d, blocks, s);
+    }
+}
+
+int march_cfg_index(int ry, int w, int k) {
+    for (int i = 0; i < kNumMarchCfgs; ++i)
+        if (kMarchCfgs[i].ry == ry && kMarchCfgs[i].w == w && kMarchCfgs[i].k == k) return i;
+    return -1;
+}
+
 int tr_cfg_index(int by, int wc, int d) {
     for (int i = 0; i < kNumTrCfgs; ++i)
         if (kTrCfgs[i].by == by && kTrCfgs[i].wc == wc && kTrCfgs[i].d == d) return i;
@@ -250,6 +274,10 @@ struct rd_grid {
     rd_plan eff{};                     // plan in use
     int cfg = -1;
     long long blocks[2] = {0, 0};
+    int march_rows = 0;                // register march: rows of a tile, its halo included
+    int left_cfg = -1;                 // its slab shape for single steps (-1: the march's own)
+    long long left_blocks = 0;
+    int variant = 0;                   // register march: MARCH_*
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gchunk = 0;
     double* d_part = nullptr;
@@ -299,8 +327,124 @@ void fill_mirror(StepArgs& a, int f) {
     a.held[f] = 0;
 }
 
+// Lane geometry of a register-march shape on a grid: the number of x tiles
+// that takes the fewest workgroups (one tile: whole rows; more: a halo lane on
+// each side, which needs rows of whole lanes on a periodic axis).  l = 0: none.
+struct MarchGeom { int l, halo, tx, by, by1; };
+MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
+    MarchGeom best{};
+    const int nx4 = (nx + kMarchVX - 1) / kMarchVX, t = 64 * c.w;
+    long long best_n = 0;
+    for (int tx = 1; tx <= nx4 && tx <= 4096; ++tx) {
+        const int halo = tx > 1 ? 1 : 0, l = (nx4 + tx - 1) / tx + 2 * halo;
+        if (l > t) continue;
+        if (l < kMarchMinLanes || (halo && periodic_x && nx % kMarchVX != 0)) break;
+        const int rows = t / l * c.ry, by = rows - 2 * c.k;
+        if (by < 1) continue;
+        const long long n = (long long)((nx4 + l - 2 * halo - 1) / (l - 2 * halo)) * ((ny + by - 1) / by);
+        if (best.l == 0 || n < best_n) {
+            best = MarchGeom{l, halo, (nx4 + l - 2 * halo - 1) / (l - 2 * halo), by, rows - 2};
+            best_n = n;
+        }
+    }
+    return best;
+}
+
+// Predicted time of one launch of a register march, in microseconds: the
+// workgroups a CU holds, in rounds, each plane of a round taking the vector
+// issue of the CU's workgroups or, where that is less, a plane's latency (loads,
+// barrier, exchange); and the time of the bytes, part of the halo reads among
+// them (the caches give the rest); the two combined as they overlap in part.
+struct MarchCost {
+    double instr;             // vector instructions per cell and plane, four clocks each at 2.4 GHz
+    double latency, launch;   // us of a plane, of a launch
+    double fill;              // planes the start of a march costs
+    double tbs;               // TB/s of the bytes
+    double halo_xy, halo_z;   // share of the halo reads that reach memory
+    int halo;                 // rows and planes a tile needs on each side
+    int extra;                // planes a march computes beyond its chunk
+    double cell_bytes;        // of the fields, read (and as many written)
+    long long lds;            // per workgroup
+    int vgprs;
+};
+double march_cost(const MarchCost& k, int ry, int w, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz, int cz) {
+    const int cus = num_cus();
+    const double issue = k.instr * ry * kMarchVX * w / 2400.0;           // a plane of one workgroup, four SIMDs
+    const int held = std::max(1, std::min(int(160 * 1024 / k.lds), 512 / ((k.vgprs + 7) / 8 * 8) * 4 / w));
+    const long long wg = (long long)m.tx * ((ny + m.by - 1) / m.by) * ((nz + cz - 1) / cz);
+    const double planes = cz + k.extra + k.fill;
+    const long long slots = (long long)cus * held, rounds = wg / slots, rest = wg % slots;
+    double us = double(rounds) * planes * std::max(k.latency, held * issue);
+    if (rest) us += planes * std::max(k.latency, double((rest + cus - 1) / cus) * issue);
+    const double over = double(m.l) / (m.l - 2 * m.halo) * (m.by + 2 * k.halo) / m.by - 1.0;
+    const double reads = (1.0 + k.halo_xy * over) * (1.0 + k.halo_z * (k.halo + k.extra) / cz);
+    const double mem = double(nx) * ny * nz * k.cell_bytes * (1.0 + reads) / (k.tbs * 1e6);
+    return std::pow(std::pow(us, 4.0) + std::pow(mem, 4.0), 0.25) + k.launch;
+}
+
+// The constants are a fit to 27 grids from 64^3 to 512^3 with every shape and 5
+// to 14 chunk lengths each (diffusion, Brusselator, pollutant; FP32 and BF16):
+// 12 % off on average, and the plans of least predicted time within 4 % of the
+// best measured.
+double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz,
+                  int cz) {
+    const int nf = march_fields(pm), t = 64 * c.w;
+    const bool poll = pm == PM_POLL1 || pm == PM_POLL2 || pm == PM_POLL2U;
+    MarchCost k{};
+    k.instr = (nf == 1 ? (poll ? 30.0 : 12.0) : poll ? 69.0 : 38.6) * (storage == ST_F32 ? 1.0 : 1.12) * c.k;
+    k.latency = 0.81, k.launch = 1.36, k.fill = 1.95;
+    k.tbs = 5.96, k.halo_xy = 0.65, k.halo_z = 0.66;
+    k.halo = c.k;
+    k.extra = 2 * (c.k - 1);
+    k.cell_bytes = nf * double(elem_size(storage));
+    k.lds = 2LL * c.k * nf * (16LL * (c.ry == 1 ? 1 : 2) * t + 8LL * (c.w + t / kMarchMinLanes) * c.ry);
+    k.vgprs = nf * c.ry * 4 * (4 + 2 * (c.k - 1)) + 50;
+    return march_cost(k, c.ry, c.w, m, nx, ny, nz, cz);
+}
+
+bool march_axes(const StepArgs& a, int nf) {
+    // the fields of a pass share their face rules: mirror or periodic along y
+    // and z, and mirror, periodic or a fixed ghost value along x
+    for (int f = 0; f < nf; ++f) {
+        for (int k = 0; k < 6; ++k)
+            if (a.bck[f][k] != a.bck[0][k] || a.bck[f][k] == BC_HELD) return false;
+        for (int k = 2; k < 6; ++k)
+            if (a.bck[f][k] == BC_GHOST) return false;
+        if (a.bck[f][2] != a.bck[f][3] || a.bck[f][4] != a.bck[f][5]) return false;
+    }
+    return true;
+}
+
 // Decomposition of a tiled plan: fills tiles_* / cz, returns workgroups.
-long long set_tiling(StepArgs& a, const rd_plan& p) {
+long long set_tiling(StepArgs& a, const rd_plan& p, int storage = ST_F32, int pm = -1) {
+    if (p.kernel == RD_KERNEL_MARCH) {
+        const MarchGeom g = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC,
+                                       {p.ry, p.waves, p.prefetch});
+        a.mg[MG_LANES] = g.l;
+        a.mg[MG_HALO] = g.halo;
+        a.mg[MG_STEPS] = p.prefetch;
+        if (pm >= 0) {
+            // launches of one step: their own chunk length of least predicted time
+            MarchGeom g1 = g;
+            g1.by = g.by1;
+            double best = 1e300;
+            for (int n = 1; n <= 64 && n <= a.nz; ++n) {
+                const int cz = (a.nz + n - 1) / n;
+                const double us = march_time(storage, pm, {p.ry, p.waves, 1}, g1, a.nx, a.ny, a.nz, cz);
+                if (us < best) {
+                    best = us;
+                    a.mg[MG_LEFT_CZ] = cz;
+                    a.mg[MG_LEFT_CHUNKS] = (a.nz + cz - 1) / cz;
+                }
+            }
+        }
+        a.cz = (p.cz <= 0 || p.cz > a.nz) ? a.nz : p.cz;
+        a.chunks_z = (a.nz + a.cz - 1) / a.cz;
+        a.zfast = p.order == 1;
+        a.tiles_x = g.tx;
+        a.tiles_y = (a.ny + g.by - 1) / g.by;
+        return (long long)a.tiles_x * a.tiles_y * a.chunks_z;
+    }
     // LDS ring: whole rows (vx cells per lane), ry rows per workgroup; the
     // one-pass front kernel: 128-cell x tiles, ry rows per workgroup
     const bool fch = p.kernel == RD_KERNEL_FUSED, tr = p.kernel == RD_KERNEL_TRING;
@@ -364,46 +508,22 @@ int balanced_cz_k(const rd_grid* g, long long tiles, int k) {
     return best;
 }
 
-rd_plan heuristic_plan(const rd_grid* g) {
+// z chunk lengths the autotuner tries: the predicted one and those that fill
+// one to four rounds of one workgroup per CU.
+std::vector<int> march_chunks(const rd_grid* g, const MarchGeom& m, int predicted) {
+    std::vector<int> czs = {predicted};
+    for (int o = 1; o <= 4; ++o) {
+        const int chunks = int(o * num_cus() / (m.tx * ((g->ny + m.by - 1) / m.by)));
+        const int cz = chunks < 1 ? 0 : int((g->nz + chunks - 1) / chunks);
+        if (cz > 0 && std::find(czs.begin(), czs.end(), cz) == czs.end()) czs.push_back(cz);
+    }
+    return czs;
+}
+
+// The slab shape that wastes the fewest lanes and rows.
+rd_plan slab_plan(const rd_grid* g) {
     rd_plan best{};
     best.kernel = RD_KERNEL_DIRECT;
-    if (g->model == RD_MODEL_FRONT_CH && !g->args[0][0].s19) {
-        // the one-pass front kernel, its largest shape for this storage
-        for (int i = 0; i < kNumFchCfgs; ++i) {
-            if (!fch_ok(g->storage, i)) continue;
-            rd_plan p{};
-            p.kernel = RD_KERNEL_FUSED;
-            p.vx = kFchCfgs[i].wm;
-            p.ry = kFchCfgs[i].by;
-            p.waves = kFchCfgs[i].wu;
-            p.prefetch = kFchCfgs[i].d;
-            const long long tiles = ((g->nx + kFchTile - 1) / kFchTile) * ((g->ny + p.ry - 1) / p.ry);
-            p.cz = balanced_cz(g, tiles);
-            int cfg = -1;
-            if (check_plan(g, p, &cfg) == RD_OK) return p;
-        }
-    }
-    if (g->args[0][0].s19) {
-        // 19-point: the first LDS-ring shape this grid and model take, with
-        // z chunks that give about two workgroups per CU; else direct
-        for (int i = 0; i < kNumLdsCfgs; ++i) {
-            const LdsCfg c = kLdsCfgs[i];
-            bool ok = ring_row_fits(g, c.nch);
-            for (int k = 0; k < g->npass; ++k) ok = ok && lds_ok(g->storage, g->pass_pm[k], i);
-            if (!ok) continue;
-            best.kernel = RD_KERNEL_LDS;
-            best.vx = 4 * c.nch;
-            best.ry = c.by;
-            best.waves = c.wc;
-            best.prefetch = c.d;
-            const int yblocks = (g->ny + c.by - 1) / c.by;
-            const int chunks = std::max(1, 2 * num_cus() / yblocks);
-            const int cz = (g->nz + chunks - 1) / chunks;
-            best.cz = cz < g->nz ? cz : 0;
-            break;
-        }
-        return best;
-    }
     double best_score = 1e30;
     unsigned mask = ~0u;
     for (int k = 0; k < g->npass; ++k) mask &= block_mask(g->storage, g->pass_pm[k]);
@@ -433,6 +553,69 @@ rd_plan heuristic_plan(const rd_grid* g) {
     return best;
 }
 
+// The register-march shape (-1: any) and chunk length of least predicted time
+// per step; false if no shape takes the grid and its model.
+bool march_plan(const rd_grid* g, int shape, rd_plan* out) {
+    double best = 1e300;
+    for (int i = 0; i < kNumMarchCfgs; ++i) {
+        if (shape >= 0 && i != shape) continue;
+        const MarchCfg c = kMarchCfgs[i];
+        rd_plan p{};
+        p.kernel = RD_KERNEL_MARCH;
+        p.vx = kMarchVX;
+        p.ry = c.ry;
+        p.waves = c.w;
+        p.prefetch = c.k;
+        int cfg = -1;
+        if (check_plan(g, p, &cfg) != RD_OK) continue;
+        const StepArgs& a = g->args[0][0];
+        const MarchGeom m = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, c);
+        for (int n = 1; n <= 64 && n <= g->nz; ++n) {
+            p.cz = int((g->nz + n - 1) / n);
+            double us = 0.0;
+            for (int k = 0; k < g->npass; ++k)
+                us += march_time(g->storage, g->pass_pm[k], c, m, g->nx, g->ny, g->nz, p.cz);
+            if (us / c.k < best) {
+                best = us / c.k;
+                *out = p;
+            }
+        }
+    }
+    return best < 1e300;
+}
+
+rd_plan heuristic_plan(const rd_grid* g) {
+    rd_plan best{};
+    best.kernel = RD_KERNEL_DIRECT;
+    // The register march wherever it applies: on every grid measured it beat
+    // the slab this rule chose before, and the best of the other plans
+    // (us per step, FP32: diffusion 512^3 77 against 189, Brusselator 256^3 28
+    // against 44, pollutant 512x512x128 171 against 218, diffusion 64^3 2.5
+    // against 6.1).
+    if (g->model != RD_MODEL_FRONT_CH && march_plan(g, -1, &best)) return best;
+    if (g->args[0][0].s19) {
+        // 19-point: the first LDS-ring shape this grid and model take, with
+        // z chunks that give about two workgroups per CU; else direct
+        for (int i = 0; i < kNumLdsCfgs; ++i) {
+            const LdsCfg c = kLdsCfgs[i];
+            bool ok = ring_row_fits(g, c.nch);
+            for (int k = 0; k < g->npass; ++k) ok = ok && lds_ok(g->storage, g->pass_pm[k], i);
+            if (!ok) continue;
+            best.kernel = RD_KERNEL_LDS;
+            best.vx = 4 * c.nch;
+            best.ry = c.by;
+            best.waves = c.wc;
+            best.prefetch = c.d;
+            const int yblocks = (g->ny + c.by - 1) / c.by;
+            const int chunks = std::max(1, 2 * num_cus() / yblocks);
+            const int cz = (g->nz + chunks - 1) / chunks;
+            best.cz = cz < g->nz ? cz : 0;
+            break;
+        }
+        return best;
+    }
+    return slab_plan(g);
+}
 std::mutex g_tune_mu;
 // autotuned plans by (nx, ny, nz, species, model, stencil and integrator, storage)
 std::map<std::tuple<int64_t, int64_t, int64_t, int, int, int>, rd_plan> g_tune_cache;
@@ -501,6 +684,29 @@ int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
         *cfg_out = cfg;
         return RD_OK;
     }
+    if (p.kernel == RD_KERNEL_MARCH) {
+        const int cfg = p.vx == kMarchVX ? march_cfg_index(p.ry, p.waves, p.prefetch) : -1;
+        if (cfg < 0) return fail(RD_EINVAL, "register-march shape not available (vx must be 4)");
+        if (g->integrator >= RD_RK2 || g->sr_mode != RD_ROUND_NEAREST)
+            return fail(RD_EINVAL, "register-march plans take forward Euler and rounding to nearest");
+        if (p.cz < 0) return fail(RD_EINVAL, "cz must be >= 0");
+        if (g->ny < p.prefetch || g->nz < p.prefetch || g->plane * int64_t(elem_size(g->storage)) >= (1LL << 31))
+            return fail(RD_EINVAL, "grid too small or its planes too large for the register march");
+        for (int k = 0; k < g->npass; ++k) {
+            if (!march_ok(g->storage, g->pass_pm[k], cfg))
+                return fail(RD_EINVAL, "register-march shape not compiled for this model and storage");
+            const StepArgs& a = g->args[0][k];
+            bool same = true;             // one launch variant serves every pass
+            for (int j = 0; j < 6; ++j) same = same && a.bck[0][j] == g->args[0][0].bck[0][j];
+            if (!same || !march_axes(a, march_fields(g->pass_pm[k])))
+                return fail(RD_EINVAL, "the register march takes fields that share mirror or periodic faces "
+                                       "(fixed ghosts along x only)");
+            if (march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, kMarchCfgs[cfg]).l == 0)
+                return fail(RD_EINVAL, "the register march has no tile for this grid");
+        }
+        *cfg_out = cfg;
+        return RD_OK;
+    }
     if (p.kernel == RD_KERNEL_LDS2) {
         const int cfg = (p.vx == 4 || p.vx == 8) ? lds2_cfg_index(p.vx / 4, p.ry, p.waves, p.prefetch) : -1;
         if (cfg < 0) return fail(RD_EINVAL, "two-step LDS ring shape not available");
@@ -520,6 +726,11 @@ int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
     if (p.cz < 0) return fail(RD_EINVAL, "cz must be >= 0");
     *cfg_out = cfg;
     return RD_OK;
+}
+
+// The one-pass front step: the update pass's arguments, one launch.
+bool one_pass(const rd_grid* g) {
+    return g->eff.kernel == RD_KERNEL_FUSED;
 }
 
 // Resolve the plan in use, fill tiling into the argument copies, upload them.
@@ -545,14 +756,41 @@ int apply_plan(rd_grid* g) {
         for (int k = 0; k < g->npass; ++k) {
             StepArgs& a = g->args[par][k];
             if (p.kernel == RD_KERNEL_TILED || p.kernel == RD_KERNEL_BLOCK || p.kernel == RD_KERNEL_LDS ||
-                p.kernel == RD_KERNEL_LDS2 || p.kernel == RD_KERNEL_FUSED || p.kernel == RD_KERNEL_TRING) {
-                g->blocks[k] = set_tiling(a, p);
+                p.kernel == RD_KERNEL_LDS2 || p.kernel == RD_KERNEL_FUSED || p.kernel == RD_KERNEL_TRING ||
+                p.kernel == RD_KERNEL_MARCH) {
+                g->blocks[k] = set_tiling(a, p, g->storage, g->pass_pm[k]);
+                if (p.kernel == RD_KERNEL_MARCH) {
+                    const bool per = a.bck[0][0] == BC_PERIODIC;
+                    const MarchGeom mg = march_geom(a.nx, a.ny, per, kMarchCfgs[cfg]);
+                    g->march_rows = mg.by + 2 * p.prefetch;
+                    g->variant = a.nx % kMarchVX != 0 ? MARCH_RAGGED
+                                 : 64 % mg.l != 0 || (per && mg.halo == 0 && mg.l != 64) ? MARCH_EDGES : MARCH_PLAIN;
+                    if (a.bck[0][0] == BC_MIRROR && a.bck[0][1] == BC_MIRROR) g->variant |= MARCH_MIRROR;
+                }
                 (void)set_tiling(g->rk_args[par][k], p);
                 (void)set_tiling(g->rk3_args[par][k], p);
             } else {
                 g->blocks[k] = 0;
             }
         }
+    // One step of a large FP32 field alone moves as many bytes in a march as in
+    // the slabs, and more in its halos: beyond the 256 MB of the last cache the
+    // slabs are the faster single step (diffusion 512^3: 210 against 238 us;
+    // 256^3, within the cache: 26 against 24).  Their arguments take the place
+    // of the Runge-Kutta stage's, which such a plan has no use for.
+    g->left_cfg = -1;
+    if (p.kernel == RD_KERNEL_MARCH && g->npass == 1 && g->storage == RD_F32 &&
+        march_fields(g->pass_pm[0]) == 1 && 2 * g->plane * g->nz * 4 > (256LL << 20)) {
+        const rd_plan sp = slab_plan(g);
+        int c = -1;
+        if (sp.kernel == RD_KERNEL_BLOCK && check_plan(g, sp, &c) == RD_OK) {
+            for (int par = 0; par < 2; ++par) {
+                g->rk_args[par][0] = g->args[par][0];
+                g->left_blocks = set_tiling(g->rk_args[par][0], sp);
+            }
+            if (g->left_blocks <= 0x7fffffffLL) g->left_cfg = c;
+        }
+    }
     for (int k = 0; k < g->npass; ++k)
         if (g->blocks[k] > 0x7fffffffLL)
             return fail(RD_EINVAL, "too many workgroups for this plan");
@@ -563,8 +801,8 @@ int apply_plan(rd_grid* g) {
     if (g->model == RD_MODEL_FRONT_CH)
         for (int par = 0; par < 2; ++par)
             for (auto* set : {&g->args, &g->rk_args, &g->rk3_args}) {
-                (*set)[par][0].clk_pass = p.kernel == RD_KERNEL_FUSED ? 0 : 1;
-                (*set)[par][1].clk_pass = p.kernel == RD_KERNEL_FUSED ? 1 : 0;
+                (*set)[par][0].clk_pass = one_pass(g) ? 0 : 1;
+                (*set)[par][1].clk_pass = one_pass(g) ? 1 : 0;
             }
     drop_graphs(g);
     RD_HIP(hipMemcpy(g->d_args, g->args, sizeof(g->args), hipMemcpyHostToDevice));
@@ -573,10 +811,23 @@ int apply_plan(rd_grid* g) {
     return RD_OK;
 }
 
-// The one-pass front step: the update pass's arguments, one launch.
-bool one_pass(const rd_grid* g) { return g->eff.kernel == RD_KERNEL_FUSED; }
+
+// One launch of `steps` steps of the register march.
+int launch_march_steps(rd_grid* g, int parity, int steps) {
+    for (int k = 0; k < g->npass; ++k) {
+        const StepArgs& a = g->args[parity][k];
+        const int by = g->march_rows - 2 * steps;
+        const int chunks = steps == a.mg[MG_STEPS] ? a.chunks_z : a.mg[MG_LEFT_CHUNKS];
+        const long long blocks = (long long)a.tiles_x * ((a.ny + by - 1) / by) * chunks;
+        const hipError_t e = launch_march(g->storage, g->pass_pm[k], g->cfg, steps, g->variant,
+                                          g->d_args + parity * 2 + k, blocks, g->stream);
+        if (e != hipSuccess) return fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
+    }
+    return RD_OK;
+}
 
 int launch_one_step(rd_grid* g, int parity) {
+    if (g->eff.kernel == RD_KERNEL_MARCH) return launch_march_steps(g, parity, g->eff.prefetch);
     if (one_pass(g)) {
         const hipError_t e = launch_fch(g->storage, g->cfg, g->args[parity][1], g->d_args + parity * 2 + 1,
                                         g->blocks[1], g->stream);
@@ -624,11 +875,60 @@ int launch_rk_step(rd_grid* g) {
     return rc;
 }
 
-int build_graph(rd_grid* g, int parity, int launches, hipGraphExec_t* out) {
+// Time steps one launch of the plan advances.
+int steps_per_launch(const rd_grid* g) {
+    return g->eff.kernel == RD_KERNEL_LDS2 ? 2 : g->eff.kernel == RD_KERNEL_MARCH ? g->eff.prefetch : 1;
+}
+
+// What is left of a count that is not a multiple of the plan's steps per
+// launch: one launch of the returned number of steps.
+int launch_left(rd_grid* g, int parity, int64_t n, int* rc) {
+    if (g->eff.kernel == RD_KERNEL_MARCH) {
+        const int steps = n >= 2 && g->eff.prefetch > 2 ? 2 : 1;
+        if (steps == 1 && g->left_cfg >= 0) {
+            const hipError_t e = launch_pass(g->storage, g->pass_pm[0], RD_KERNEL_BLOCK, g->left_cfg,
+                                             g->rk_args[parity][0], g->d_args + 4 + parity * 2, g->left_blocks,
+                                             g->stream);
+            *rc = e == hipSuccess ? RD_OK : fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
+            return 1;
+        }
+        *rc = launch_march_steps(g, parity, steps);
+        return steps;
+    }
+    *rc = RD_OK;
+    for (int k = 0; k < g->npass && *rc == RD_OK; ++k) {
+        const hipError_t e = launch_pass(g->storage, g->pass_pm[k], RD_KERNEL_DIRECT, -1, g->args[parity][k],
+                                         g->d_args + parity * 2 + k, 0, g->stream);
+        if (e != hipSuccess) *rc = fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
+    }
+    return 1;
+}
+
+// The launches of n Euler steps from the state in *parity, which each flips.
+int launch_steps(rd_grid* g, int64_t n, int* parity) {
+    const int sp = steps_per_launch(g);
+    for (; n >= sp; n -= sp) {
+        const int rc = launch_one_step(g, *parity);
+        if (rc) return rc;
+        *parity ^= 1;
+    }
+    while (n > 0) {
+        int rc = RD_OK;
+        n -= launch_left(g, *parity, n, &rc);
+        if (rc) return rc;
+        *parity ^= 1;
+    }
+    return RD_OK;
+}
+
+// A graph of `steps` steps from the state in `parity`.
+int build_graph(rd_grid* g, int parity, int steps, hipGraphExec_t* out) {
     RD_HIP(hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal));
     int rc = RD_OK;
-    for (int i = 0; i < launches && rc == RD_OK; ++i)
-        rc = g->integrator >= RD_RK2 ? launch_rk_step(g) : launch_one_step(g, (parity + i) & 1);
+    if (g->integrator >= RD_RK2)
+        for (int i = 0; i < steps && rc == RD_OK; ++i) rc = launch_rk_step(g);
+    else
+        rc = launch_steps(g, steps, &parity);
     hipGraph_t graph = nullptr;
     const hipError_t e = hipStreamEndCapture(g->stream, &graph);
     if (rc != RD_OK) {
@@ -639,19 +939,6 @@ int build_graph(rd_grid* g, int parity, int launches, hipGraphExec_t* out) {
     const hipError_t ei = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (ei != hipSuccess) return fail(RD_EDEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(ei));
-    return RD_OK;
-}
-
-// Time steps one launch of the plan advances.
-int steps_per_launch(const rd_grid* g) { return g->eff.kernel == RD_KERNEL_LDS2 ? 2 : 1; }
-
-// One step with the direct kernel (the odd step left over by a two-step plan).
-int launch_direct_step(rd_grid* g, int parity) {
-    for (int k = 0; k < g->npass; ++k) {
-        const hipError_t e = launch_pass(g->storage, g->pass_pm[k], RD_KERNEL_DIRECT, -1, g->args[parity][k],
-                                         g->d_args + parity * 2 + k, 0, g->stream);
-        if (e != hipSuccess) return fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
-    }
     return RD_OK;
 }
 
@@ -679,12 +966,11 @@ int step_grid(rd_grid* g, int64_t n) {
     }
     const int chunk = g->eff.graph_chunk;          // steps per graph (even)
     const int sp = steps_per_launch(g);
-    const int launches = chunk / sp;               // launches per graph
     if (chunk >= 2 && g->stream != nullptr && n >= chunk) {
         if (g->gchunk != chunk) {
             drop_graphs(g);
             for (int par = 0; par < 2; ++par) {
-                const int rc = build_graph(g, par, launches, &g->gexec[par]);
+                const int rc = build_graph(g, par, chunk, &g->gexec[par]);
                 if (rc) {
                     drop_graphs(g);
                     return rc;
@@ -692,23 +978,15 @@ int step_grid(rd_grid* g, int64_t n) {
             }
             g->gchunk = chunk;
         }
+        const int left = chunk % sp;               // (two steps a launch, then one)
+        const int launches = chunk / sp + (g->eff.kernel == RD_KERNEL_MARCH ? (left + 1) / 2 : left);
         while (n >= chunk) {
             RD_HIP(hipGraphLaunch(g->gexec[g->cur], g->stream));
             g->cur ^= launches & 1;
             n -= chunk;
         }
     }
-    for (; n >= sp; n -= sp) {
-        const int rc = launch_one_step(g, g->cur);
-        if (rc) return rc;
-        g->cur ^= 1;
-    }
-    if (n > 0) {
-        const int rc = launch_direct_step(g, g->cur);
-        if (rc) return rc;
-        g->cur ^= 1;
-    }
-    return RD_OK;
+    return launch_steps(g, n, &g->cur);
 }
 
 }  // namespace
@@ -1159,6 +1437,17 @@ extern "C" int rd_set_rounding(rd_grid* g, int32_t mode, uint64_t seed) {
     if (mode == RD_ROUND_STOCHASTIC && g->has_model && g->integrator >= RD_RK2)
         return fail(RD_EINVAL, "stochastic rounding takes forward Euler steps");
     RD_HIP(hipStreamSynchronize(g->stream));
+    if (g->has_model && g->plan.kernel == RD_KERNEL_MARCH) {
+        // a plan asked for by name has to take the rounding
+        const int old = g->sr_mode;
+        int cfg = -1;
+        g->sr_mode = mode;
+        const int rc = check_plan(g, g->plan, &cfg);
+        if (rc) {
+            g->sr_mode = old;
+            return rc;
+        }
+    }
     g->sr_mode = mode;
     g->sr_seed = uint32_t(seed);
     if (!g->has_model) return RD_OK;
@@ -1169,11 +1458,7 @@ extern "C" int rd_set_rounding(rd_grid* g, int32_t mode, uint64_t seed) {
                 a->sr_key = g->sr_seed;
             }
         }
-    drop_graphs(g);
-    RD_HIP(hipMemcpy(g->d_args, g->args, sizeof(g->args), hipMemcpyHostToDevice));
-    RD_HIP(hipMemcpy(g->d_args + 4, g->rk_args, sizeof(g->rk_args), hipMemcpyHostToDevice));
-    RD_HIP(hipMemcpy(g->d_args + 8, g->rk3_args, sizeof(g->rk3_args), hipMemcpyHostToDevice));
-    return RD_OK;
+    return apply_plan(g);      // the plan in use depends on the rounding; uploads the arguments
 }
 
 extern "C" int rd_write_field(rd_grid* g, int32_t species, const void* src, int32_t src_dtype,
@@ -1499,6 +1784,16 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
                 p.order = order;
                 cands.push_back(p);
             }
+        }
+    }
+    for (int i = 0; i < kNumMarchCfgs && !g->args[0][0].s19 && g->model != RD_MODEL_FRONT_CH; ++i) {
+        rd_plan p{};
+        if (!march_plan(g, i, &p)) continue;
+        const StepArgs& a = g->args[0][0];
+        const MarchGeom m = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, kMarchCfgs[i]);
+        for (int cz : march_chunks(g, m, p.cz)) {
+            p.cz = cz;
+            cands.push_back(p);
         }
     }
     for (int i = 0; i < kNumLds2Cfgs && g->npass == 1; ++i) {

@@ -1,0 +1,526 @@
+// rd_march.hpp -- K time steps per launch: a z march that keeps its planes in
+// registers (temporal blocking; section 2's step, Eq. (5), taken K times between
+// one read and one write of every species).
+//
+// What bounds a step is memory first: one read and one write of every species.
+// A launch of K steps moves them once, so the bound becomes the vector
+// arithmetic, repeated in the halos of the tiles; K, the rows of a lane and the
+// waves of a workgroup trade one against the other.
+//
+// A lane owns four cells of a row (one 16-byte load in FP32) in RY rows; L lanes
+// make a tile row and the T = 64 W threads of a workgroup T / L groups of RY
+// rows, so rows of any length fill the waves (a wave is not a row).  A tile
+// stores K rows less on each side than it loads, K cells less at an inner x
+// edge (one halo lane), and marches K planes more: level l of plane p - l + 1
+// (level 0: the planes loaded) is formed in iteration p, all levels one after
+// the other, so an iteration loads one plane and stores one plane K steps on.
+//   z neighbours: registers -- three planes of level 0 and one in flight, two
+//     of each further level (a new value takes the place of the oldest);
+//   y neighbours: registers inside a lane; the lane's first and last row pass
+//     through LDS, every level and field in one exchange per iteration (two
+//     buffers by parity, so one barrier);
+//   x neighbours: the next lane by DPP; at the ends of a wave through LDS in the
+//     same exchange (XEX; not needed where rows lie inside a wave).
+// Loads and stores are buffer accesses of one plane, 32-bit offsets per lane
+// formed once; a lane that stores nothing has an offset out of the plane, which
+// the hardware drops, so the loop has no branch around its stores and the
+// counts of accesses in flight stay exact.
+//
+// Face rules.  Along y and z a mirror face is the reflection of the rows
+// (planes) at it: the reflected rows, computed as any other, come out equal to
+// the rows they mirror bit for bit, since a row's two neighbours are added to
+// each other first; a periodic face wraps.  So rows and planes outside the grid
+// need no code but the index they are loaded from.  Along x the rule is applied
+// at use, at every level: mirror, periodic, or a fixed ghost value.  Held layers
+// and fixed ghosts along y and z are left to the other plans.
+// Values between levels are rounded to the storage type, as a step that stored
+// them would; every cell goes through the model's own cell function, so K steps
+// give the bits of K launches of one.
+//
+// Measured (us per step, default plans; one step per launch, the best plan
+// before, against this): diffusion 512^3 FP32 189 -> 77 (K 4: 1740 Gcell/s, 2.2
+// times what the bytes of single steps would allow at 8 TB/s), BF16 121 -> 68;
+// Brusselator 256^3 FP32 44.3 -> 28.0, BF16 42.3 -> 28.2; pollutant 512x512x128
+// FP32 218 -> 170; small grids, where a launch is the latency of its chain of
+// loads: diffusion 64^3 6.1 -> 2.5, Brusselator 101x90x77 10.2 -> 4.9.  At
+// diffusion 512^3, K 2, the vector units were busy 59 % of the time and 5.3 TB/s
+// moved; non-temporal stores gained 2 % there and cost the Brusselator, whose
+// fields stay in the last cache, 20 %.
+#pragma once
+
+#include "rd_march_cfg.hpp"
+
+namespace rdk {
+
+#ifdef __HIP_DEVICE_COMPILE__
+typedef unsigned march_u4 __attribute__((ext_vector_type(4)));
+typedef unsigned march_u2 __attribute__((ext_vector_type(2)));
+typedef float march_f4 __attribute__((ext_vector_type(4)));
+#endif
+
+// Index of grid row / plane q, at most n beyond either face of a periodic or
+// mirror axis of n cells: wrapped, or reflected (-1 is 0, -2 is 1, ..).
+__device__ __forceinline__ int march_index(int q, int n, bool periodic) {
+    const int lo = periodic ? q + n : -1 - q, hi = periodic ? q - n : 2 * n - 1 - q;
+    return q < 0 ? lo : q >= n ? hi : q;
+}
+
+// Element e (0 .. 2) of a lane's cells, by value: a select, not an address.
+__device__ __forceinline__ float march_elem(int e, float c0, float c1, float c2) {
+    return e == 0 ? c0 : e == 1 ? c1 : c2;
+}
+
+// A value held in a scalar register that the compiler cannot form again by
+// reloading it.
+__device__ __forceinline__ float scopy(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(x));
+#endif
+    return x;
+}
+
+#ifdef __HIP_DEVICE_COMPILE__
+// Four loaded cells as FP32, and four results as stored (offset ~0: dropped).
+template <class S, class Raw>
+__device__ __forceinline__ void march_unpack(const Raw& q, float (&v)[4]) {
+    using T = typename S::T;
+    if constexpr (sizeof(T) == 4) {
+        v[0] = __uint_as_float(q.x);
+        v[1] = __uint_as_float(q.y);
+        v[2] = __uint_as_float(q.z);
+        v[3] = __uint_as_float(q.w);
+    } else {
+        v[0] = S::up(T(q.x & 0xffffu));
+        v[1] = S::up(T(q.x >> 16));
+        v[2] = S::up(T(q.y & 0xffffu));
+        v[3] = S::up(T(q.y >> 16));
+    }
+}
+template <class S>
+__device__ __forceinline__ void march_store(const float (&o)[4], __amdgpu_buffer_rsrc_t ws, unsigned so) {
+    if constexpr (sizeof(typename S::T) == 4) {
+        march_u4 d;
+        d.x = __float_as_uint(o[0]);
+        d.y = __float_as_uint(o[1]);
+        d.z = __float_as_uint(o[2]);
+        d.w = __float_as_uint(o[3]);
+        __builtin_amdgcn_raw_buffer_store_b128(d, ws, so, 0, 0);
+    } else {
+        march_u2 d;
+        d.x = S::down2(o[0], o[1]);
+        d.y = S::down2(o[2], o[3]);
+        __builtin_amdgcn_raw_buffer_store_b64(d, ws, so, 0, 0);
+    }
+}
+#endif
+
+// f(row) for every row of a lane: inner rows first, then the first and last.
+template <int RY, int I = 0, class F>
+__device__ __forceinline__ void march_rows(F&& f) {
+    if constexpr (I < RY) {
+        f(std::integral_constant<int, (I < RY - 2 ? I + 1 : I == RY - 1 ? RY - 1 : 0)>{});
+        march_rows<RY, I + 1>(f);
+    }
+}
+
+// N contiguous floats to / from LDS (scalar accesses, which the compiler
+// merges: vectors built here from single cells kept the planes they come from
+// in memory).
+template <int N>
+__device__ __forceinline__ void march_lds_put(RD_LDS float* p, const float (&e)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = e[i];
+}
+template <int N>
+__device__ __forceinline__ void march_lds_get(const RD_LDS float* p, float (&e)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = p[i];
+}
+
+template <int NF> struct MarchConst {
+    float kx[NF], ky[NF], kz[NF], kc[1];
+    float p[3];
+    float dt;
+    __device__ __forceinline__ explicit MarchConst(const StepArgs& a) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            kx[f] = scopy(a.kx[f]);
+            ky[f] = scopy(a.ky[f]);
+            kz[f] = scopy(a.kz[f]);
+        }
+        kc[0] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) p[i] = scopy(a.p[i]);
+        dt = scopy(a.dt);
+    }
+};
+
+template <class M, class S, int RY, int W, int K, bool XEX, bool RAG, bool MIR>
+__global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restrict__ pa) {
+    constexpr int NF = M::NF, T = 64 * W, ES = int(sizeof(typename S::T));
+    static_assert(M::NO == NF, "every field is stored");
+    constexpr int NR = RY == 1 ? 1 : 2;              // boundary rows of a lane
+    constexpr int NE = K * NF;                        // values of an edge slot: by level, then field
+    constexpr int NX = (W + T / kMarchMinLanes) * RY + 1;   // edge slots of one side, the last the face values
+    __shared__ __attribute__((aligned(16))) float rows_s[2 * K * NF * NR * T * 4];
+    __shared__ __attribute__((aligned(16))) float edge_s[2 * 2 * NX * NE];
+#ifdef __HIP_DEVICE_COMPILE__
+    const StepArgs& a = *pa;
+    RD_LDS float* rows_l = (RD_LDS float*)&rows_s[0];
+    RD_LDS float* edge_l = (RD_LDS float*)&edge_s[0];
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+
+    // ---- the tile ---------------------------------------------------------
+    const int L = a.mg[MG_LANES], halo = a.mg[MG_HALO], G = T / L;
+    const int BY = G * RY - 2 * K;                   // rows stored
+    const bool left_over = a.mg[MG_STEPS] != K;
+    const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz, chunks = left_over ? a.mg[MG_LEFT_CHUNKS] : a.chunks_z;
+    const int tiles_y = (a.ny + BY - 1) / BY;
+    int b = xcd_tile(blockIdx.x, gridDim.x);
+    int tx, ty, tz;
+    if (a.zfast) {
+        tz = b % chunks;
+        b /= chunks;
+        tx = b % a.tiles_x;
+        ty = b / a.tiles_x;
+    } else {
+        tx = b % a.tiles_x;
+        b /= a.tiles_x;
+        ty = b % tiles_y;
+        tz = b / tiles_y;
+    }
+    const int yb = ty * BY, z0 = tz * cz, z1 = min(z0 + cz, a.nz);
+    const int yg = t / L, x4 = t - yg * L;
+    const bool perx = a.bck[0][0] == BC_PERIODIC, pery = a.bck[0][2] == BC_PERIODIC,
+               perz = a.bck[0][4] == BC_PERIODIC;
+    const int x = (tx * (L - 2 * halo) + x4 - halo) * 4;
+    int xm = x;                                      // column loaded
+    if (perx && halo) xm = x < 0 ? x + a.nx : x >= a.nx ? x - a.nx : x;
+    xm = min(max(xm, 0), a.pitch - 4);
+    const bool wrap = perx && !halo;                 // the row's ends meet through LDS
+    const int e_last = (a.nx - 1) & 3;               // element of the row's last cell
+    const bool first = x == 0 && !(perx && halo), last = x <= a.nx - 1 && x > a.nx - 5 && !(perx && halo);
+    const bool rot = !XEX && perx;                  // rows of one wave: the lane rotation wraps them
+    const bool own_l = first && a.bck[0][0] == BC_MIRROR, in_l = first && a.bck[0][0] != BC_MIRROR && !rot;
+    const bool mir_r = a.bck[0][1] == BC_MIRROR;
+    const bool own_r = last && mir_r && !RAG, in_r = last && !mir_r && !RAG && !rot;
+    // RAG: the cell after the row's last, in the last lane, holds what is
+    // beyond the face
+    bool after[3];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) after[i - 1] = last && e_last + 1 == i;
+    const bool stored_x = x4 >= halo && x4 < L - halo && x >= 0 && x < a.nx && yg < G;
+
+    unsigned lo[RY], so[RY];                         // byte offsets in a plane: loaded, stored (~0: not stored)
+    int yr[M::SOURCES ? RY : 1];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+        const int yl = yg * RY + r, y = yb - K + yl;
+        const int ym = march_index(min(max(y, -K), a.ny - 1 + K), a.ny, pery);
+        lo[r] = unsigned(ym * a.pitch + xm) * ES;
+        so[r] = stored_x && yl >= K && yl < K + BY && y < a.ny ? unsigned(y * a.pitch + x) * ES : 0x80000000u;
+        if constexpr (M::SOURCES) yr[r] = ym;
+    }
+
+    // ---- exchange slots ------------------------------------------------------
+    // boundary rows: slot t; the rows above and below are those of t -+ L
+    const int up_t = max(t - L, 0), dn_t = min(t + L, T - 1);
+    auto row_at = [&](int par, int l, int f, int k, int th) __attribute__((always_inline)) {
+        return rows_l + ((((par * K + l) * NF + f) * NR + k) * T + th) * 4;
+    };
+    // x edges: where this lane's first / last cell goes (-1: nowhere) and where
+    // its outer neighbours come from -- the next wave, the row's other end
+    // (slot W + row group) or the face's value (the last slot)
+    constexpr int FACE = MIR ? 0 : NX - 1;            // (mirror faces take no value)
+    int ef = -1, el = -1, rf = 0, rl = 0;
+    if (lane == 0 && x4 != 0) ef = rf = w * RY;
+    if (lane == 63 && x4 != L - 1) el = rl = (w + 1) * RY;
+    if (first) {
+        if (wrap) ef = (W + yg) * RY;
+        rf = wrap ? (W + yg) * RY : FACE;
+    }
+    if (last) {
+        if (wrap) el = (W + yg) * RY;
+        rl = wrap ? (W + yg) * RY : FACE;
+    }
+    if (yg >= G || (w == W - 1 && lane == 63 && !last)) {
+        el = -1;
+        rl = FACE;
+    }
+    if (yg >= G) {
+        ef = -1;
+        rf = FACE;
+    }
+    // side 0 holds first cells (read as a right neighbour), side 1 last cells
+    auto edge_at = [&](int par, int side, int slot) __attribute__((always_inline)) {
+        return edge_l + ((par * 2 + side) * NX + slot) * NE;
+    };
+    if constexpr (XEX && !MIR) {
+        if (t < 4 * NE) {                            // written before the first barrier, read after it
+            const int f = t % NF, side = (t / NE) & 1;
+            edge_at(t / (2 * NE), side, FACE)[t % NE] = side ? a.bcv[f][0] : a.bcv[f][1];
+        }
+    }
+
+    const MarchConst<NF> k(a);
+    float cl[NF], cr[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        cl[f] = scopy(a.bcv[f][0]);
+        cr[f] = scopy(a.bcv[f][1]);
+    }
+
+    // ---- planes ------------------------------------------------------------
+    const long long pbytes = a.plane * ES;
+    float V[4][NF][RY][4];                           // level 0: planes p-1, p, p+1
+    float Q[K > 1 ? K - 1 : 1][2][NF][RY][4];        // levels 1 .. K-1: two planes each
+    using Raw = std::conditional_t<ES == 4, march_u4, march_u2>;
+    Raw P[NF][RY];                                   // the plane in flight
+    auto issue = [&](int p) __attribute__((always_inline)) {
+        const int pz = march_index(min(p, z1 - 1 + K), a.nz, perz);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)((const char*)a.in[f] + pz * pbytes), 0, int(pbytes), 0x00027000);
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                if constexpr (ES == 4) P[f][r] = __builtin_amdgcn_raw_buffer_load_b128(rs, lo[r], 0, 0);
+                else P[f][r] = __builtin_amdgcn_raw_buffer_load_b64(rs, lo[r], 0, 0);
+            }
+        }
+    };
+    auto take = [&](float (&v)[NF][RY][4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int r = 0; r < RY; ++r) march_unpack<S>(P[f][r], v[f][r]);
+    };
+#pragma unroll
+    for (int l = 0; l < (K > 1 ? K - 1 : 1); ++l)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int r = 0; r < RY; ++r)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) Q[l][j][f][r][i] = 0.f;
+
+    const int pa_ = z0 - (K - 1), pb_ = z1 - 1 + (K - 1);   // centre planes of level 1
+    issue(pa_ - 1);
+    take(V[0]);
+    issue(pa_);
+    take(V[1]);
+    issue(pa_ + 1);
+
+    auto export_plane = [&](int par, int l, const float (&v)[NF][RY][4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                const float(&c)[4] = v[f][j == 0 ? 0 : RY - 1];
+                lds_st4(row_at(par, l, f, j, t), c[0], c[1], c[2], c[3]);
+            }
+    };
+    // the last cell of a row in this lane
+    auto end_cell = [&](const float (&c)[4]) __attribute__((always_inline)) {
+        if constexpr (!RAG) return c[3];
+        const float ce = march_elem(e_last, c[0], c[1], c[2]);
+        return last ? ce : c[3];
+    };
+    // the row ends of every level and field, one vector per slot and row
+    auto export_edges = [&](int par, const float (&v0)[NF][RY][4], auto par_c) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par_c)::value;
+        if constexpr (XEX) {
+            if (ef >= 0) {
+                march_rows<RY>([&](auto rc) __attribute__((always_inline)) {
+                    constexpr int r = decltype(rc)::value;
+                    float e[NE];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        e[f] = v0[f][r][0];
+#pragma unroll
+                        for (int l = 1; l < K; ++l) e[l * NF + f] = Q[l - 1][PAR][f][r][0];
+                    }
+                    march_lds_put<NE>(edge_at(par, 0, ef + r), e);
+                });
+            }
+            if (el >= 0) {
+                march_rows<RY>([&](auto rc) __attribute__((always_inline)) {
+                    constexpr int r = decltype(rc)::value;
+                    float e[NE];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        e[f] = end_cell(v0[f][r]);
+#pragma unroll
+                        for (int l = 1; l < K; ++l) e[l * NF + f] = end_cell(Q[l - 1][PAR][f][r]);
+                    }
+                    march_lds_put<NE>(edge_at(par, 1, el + r), e);
+                });
+            }
+        }
+    };
+    struct Halo {
+        float up[NF][4], dn[NF][4];
+    };
+    auto import_plane = [&](int par, int l, Halo& h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            lds_ld4(row_at(par, l, f, NR - 1, up_t), h.up[f]);
+            lds_ld4(row_at(par, l, f, 0, dn_t), h.dn[f]);
+        }
+    };
+
+    // one row of the level above: centre plane v, planes vm and vp
+    auto row = [&](int r, const float (&vm)[NF][RY][4], const float (&v)[NF][RY][4], const float (&vp)[NF][4],
+                   const Halo& h, const float (&xl)[NF], const float (&xr)[NF], float wind, int src_row,
+                   float (&o)[NF][4]) __attribute__((always_inline)) {
+        float c[NF][4], left[NF], right[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[f][i] = v[f][r][i];
+            if constexpr (RAG) {
+                const float ce = march_elem(e_last, c[f][0], c[f][1], c[f][2]);
+                const float fr = MIR || mir_r ? ce : xr[f];
+#pragma unroll
+                for (int i = 1; i < 4; ++i) c[f][i] = after[i - 1] ? fr : c[f][i];
+            }
+            if constexpr (XEX) {
+                left[f] = lane_from_left(c[f][3], xl[f]);
+                right[f] = lane_from_right(c[f][0], xr[f]);
+            } else {
+                left[f] = lane_from_left_wrap(c[f][3]);
+                right[f] = lane_from_right_wrap(c[f][0]);
+            }
+            left[f] = own_l ? c[f][0] : left[f];
+            if constexpr (!RAG) right[f] = own_r ? c[f][3] : right[f];
+            if constexpr (!MIR) {
+                left[f] = in_l ? (XEX ? xl[f] : cl[f]) : left[f];
+                if constexpr (!RAG) right[f] = in_r ? (XEX ? xr[f] : cr[f]) : right[f];
+            }
+        }
+        int s0 = 0, s1 = 0;
+        if constexpr (M::SOURCES) {
+            if (src_row >= 0) {
+                s0 = cload_ptr<int>(a.src_row)[src_row + yr[r]];
+                s1 = cload_ptr<int>(a.src_row)[src_row + yr[r] + 1];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            Nb n[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                n[f].c = c[f][i];
+                n[f].xm = i > 0 ? c[f][i - 1] : left[f];
+                n[f].xp = i < 3 ? c[f][i + 1] : right[f];
+                n[f].ym = r > 0 ? v[f][r > 0 ? r - 1 : 0][i] : h.up[f][i];
+                n[f].yp = r < RY - 1 ? v[f][r < RY - 1 ? r + 1 : 0][i] : h.dn[f][i];
+                n[f].zm = vm[f][r][i];
+                n[f].zp = vp[f][i];
+            }
+            Emission<NF> em{};
+            if constexpr (M::SOURCES) {
+                if (src_row >= 0) em = cell_sources<NF>(a, xm + i, s0, s1);
+            }
+            float oi[NF];
+            M::cell(k, n, wind, em.any, em.e, oi);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) o[f][i] = oi[f];
+        }
+    };
+
+    auto plane = [&](int p, auto jc) __attribute__((always_inline)) {
+        constexpr int J = decltype(jc)::value;
+        constexpr int par = J & 1, I0 = J & 3, I1 = (J + 1) & 3, I2 = (J + 2) & 3;
+        take(V[I2]);
+        issue(p + 2);
+        export_edges(par, V[I1], std::integral_constant<int, par>{});
+        export_plane(par, 0, V[I1]);
+#pragma unroll
+        for (int l = 1; l < K; ++l) export_plane(par, l, Q[l - 1][par]);
+        // wind and source ranges of the planes the levels compute
+        float wind[K];
+        int srow[K];
+#pragma unroll
+        for (int l = 0; l < K; ++l) {
+            // (the first iterations' planes of the upper levels are not needed:
+            // any plane of the tables will do)
+            const int pz = march_index(min(max(p - l, 1 - K), a.nz + K - 2), a.nz, perz);
+            wind[l] = plane_wind<M>(a, pz);
+            srow[l] = -1;
+            if constexpr (M::SOURCES) {
+                const int q = pz * a.ny;
+                if (cload_ptr<int>(a.src_row)[q] < cload_ptr<int>(a.src_row)[q + a.ny]) srow[l] = q;
+            }
+        }
+        lds_done();
+        ring_barrier();
+        Halo h[K];
+#pragma unroll
+        for (int l = 0; l < K; ++l) import_plane(par, l, h[l]);
+        const int zo = p - (K - 1);
+        const bool put = zo >= z0 && zo < z1;
+        __amdgpu_buffer_rsrc_t ws[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            ws[f] = __builtin_amdgcn_make_buffer_rsrc((void*)((char*)a.out[f] + zo * pbytes), 0,
+                                                      put ? int(pbytes) : 0, 0x00027000);
+        // inner rows first: they need no row of another lane
+        march_rows<RY>([&](auto rc) __attribute__((always_inline)) {
+            constexpr int r = decltype(rc)::value;
+            float xl[NE], xr[NE];
+            if constexpr (XEX) {
+                march_lds_get<NE>(edge_at(par, 1, !MIR && rf == FACE ? FACE : rf + r), xl);
+                march_lds_get<NE>(edge_at(par, 0, !MIR && rl == FACE ? FACE : rl + r), xr);
+            }
+            float n[NF][4], o[NF][4];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) n[f][i] = V[I2][f][r][i];
+            float el_[NF], er_[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                el_[f] = XEX ? xl[f] : 0.f;
+                er_[f] = XEX ? xr[f] : 0.f;
+            }
+            row(r, V[I0], V[I1], n, h[0], el_, er_, wind[0], srow[0], o);
+#pragma unroll
+            for (int l = 1; l < K; ++l) {
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) n[f][i] = ES == 4 ? o[f][i] : S::up(S::down(o[f][i]));
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    el_[f] = XEX ? xl[l * NF + f] : 0.f;
+                    er_[f] = XEX ? xr[l * NF + f] : 0.f;
+                }
+                row(r, Q[l - 1][par ^ 1], Q[l - 1][par], n, h[l], el_, er_, wind[l], srow[l], o);
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) Q[l - 1][par ^ 1][f][r][i] = n[f][i];
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) march_store<S>(o[f], ws[f], so[r]);
+        });
+    };
+    for (int p = pa_; p <= pb_; p += 4) {
+        plane(p, std::integral_constant<int, 0>{});
+        if (p + 1 > pb_) break;
+        plane(p + 1, std::integral_constant<int, 1>{});
+        if (p + 2 > pb_) break;
+        plane(p + 2, std::integral_constant<int, 2>{});
+        if (p + 3 > pb_) break;
+        plane(p + 3, std::integral_constant<int, 3>{});
+    }
+#else
+    (void)pa, (void)rows_s, (void)edge_s;
+#endif
+}
+
+}  // namespace rdk

@@ -1,0 +1,158 @@
+"""The register-march plans (and the default plan, which takes them where they
+apply) against the direct plan, bit for bit: every plan forms each cell by the
+same arithmetic, so the fields must be equal at the edges of tiles, of lanes
+and of z chunks, for every face rule the plans take, whatever is left of a
+step count, and the calls they refuse must fall back."""
+import numpy as np
+import pytest
+
+from paper_1004_0480_amd import rd
+from paper_1004_0480_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MIRROR, PERIODIC = ("mirror", 0.0), ("periodic", 0.0)
+GHOST, HELD = ("ghost", 0.7), ("held", 0.6)
+# x-, x+, y faces, z faces
+FACES = {"mirror": (MIRROR, MIRROR, MIRROR, MIRROR), "periodic": (PERIODIC, PERIODIC, PERIODIC, PERIODIC),
+         "ghost_lo": (GHOST, MIRROR, MIRROR, PERIODIC), "ghost_hi": (MIRROR, GHOST, PERIODIC, MIRROR)}
+# several rows in a wave; ragged rows; a row per wave; the fewest lanes; rows
+# longer than a workgroup takes whole; the fewest rows and planes; one cell past
+# a lane
+SHAPES = [(9, 37, 64), (7, 40, 101), (20, 23, 256), (6, 33, 29), (5, 11, 2060), (4, 5, 260), (6, 9, 385)]
+
+
+def spec_of(model, shape, faces):
+    s = (W.diffusion_spec() if model == "diffusion" else W.brusselator_spec() if model == "brusselator" else
+         W.pollutant_spec(shape, 5, ns=int(model[-1]), nsrc=40))
+    if model == "diffusion":
+        s.K = [[1.0, 0.7, 0.4]]
+    xl, xh, y, z = faces
+    s.bc = [[xl, xh, y, y, z, z] for _ in range(s.ns)]
+    return s
+
+
+def run(spec, shape, fields, storage, steps, plan=None, chunk=0, rounding=None):
+    import torch
+    g = rd.Grid(shape, spec.ns, spec.h, storage, stream=torch.cuda.Stream() if chunk else None)
+    g.set_model(spec)
+    if rounding is not None:
+        g.set_rounding("stochastic", rounding)
+    if plan is not None or chunk:
+        g.set_plan(**dict(plan or {}, graph_chunk=chunk))
+    for s, f in enumerate(fields):
+        g.write(s, f)
+    for n in steps:
+        g.step(n)
+    got, used = g.read_all(np.float32), g.plan()
+    g.close()
+    return got, used
+
+
+def same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def fields_of(shape, ns, seed):
+    rng = np.random.default_rng(seed)
+    return [rng.random(shape) + 0.5 for _ in range(ns)]
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("model,shapes", [("diffusion", [(1, 8, 2), (1, 16, 2), (1, 8, 3), (1, 16, 3), (1, 8, 4)]),
+                                          ("brusselator", [(1, 8, 2), (1, 16, 2), (2, 8, 2)]),
+                                          ("pollutant4", [(1, 8, 2), (2, 8, 2)]),
+                                          ("pollutant3", [(1, 16, 2)]), ("pollutant1", [(1, 8, 4)])])
+def test_march_plans_bitwise(model, shapes, storage):
+    for shape in SHAPES:
+        for name, faces in FACES.items():
+            spec = spec_of(model, shape, faces)
+            f = fields_of(shape, spec.ns, 3)
+            ref, _ = run(spec, shape, f, storage, [7], dict(kernel="direct"))
+            for ry, w, k in shapes:
+                for cz in (0, 3):
+                    plan = dict(kernel="march", vx=4, ry=ry, waves=w, prefetch=k, cz=cz, order=cz & 1)
+                    if name == "periodic" and shape[2] % 4 and shape[2] > 256:
+                        # whole rows only (a halo lane cannot hold a ragged
+                        # wrap): too few rows fit some shapes
+                        try:
+                            got, used = run(spec, shape, f, storage, [7], plan)
+                        except rd.RDError as e:
+                            assert e.code == rd.EINVAL
+                            continue
+                    else:
+                        got, used = run(spec, shape, f, storage, [7], plan)
+                    assert used["kernel"] == 8
+                    assert same(got, ref), (model, shape, name, plan)
+
+
+def test_march_graphs_split_calls_and_left_steps():
+    shape = (12, 30, 100)
+    spec = spec_of("diffusion", shape, FACES["mirror"])
+    f = fields_of(shape, 1, 4)
+    for k, w in ((4, 8), (3, 16), (2, 8)):
+        plan = dict(kernel="march", vx=4, ry=1, waves=w, prefetch=k, cz=5)
+        ref, _ = run(spec, shape, f, "f32", [33], dict(kernel="direct"))
+        for chunk in (0, 2, 6, 10):
+            for calls in ([33], [1, 2, 3, 5, 22]):
+                got, _ = run(spec, shape, f, "f32", calls, plan, chunk)
+                assert same(got, ref), (k, chunk, calls)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+def test_default_plan_bitwise(storage):
+    """Every kind of face, also those the register march refuses (the default
+    plan then falls back), mixed between fields and passes, on small and odd
+    grids."""
+    one = [[MIRROR] * 6, [PERIODIC] * 6, [HELD, MIRROR] + [MIRROR] * 4, [MIRROR] * 4 + [HELD, GHOST],
+           [MIRROR, MIRROR, GHOST, MIRROR, MIRROR, MIRROR], [GHOST, GHOST] + [PERIODIC] * 4]
+    for shape in ((1, 1, 1), (2, 3, 40), (5, 2, 33), (3, 4, 28), (9, 21, 130), (30, 33, 37)):
+        for model in ("diffusion", "brusselator", "pollutant4"):
+            for i, bc in enumerate(one):
+                spec = spec_of(model, shape, FACES["mirror"])
+                # the last field of a model with several takes other rules
+                spec.bc = [list(bc) for _ in range(spec.ns)]
+                if spec.ns > 1 and i % 2:
+                    spec.bc[-1] = list(one[(i + 1) % len(one)])
+                f = fields_of(shape, spec.ns, 5)
+                ref, _ = run(spec, shape, f, storage, [5], dict(kernel="direct"))
+                got, used = run(spec, shape, f, storage, [5])
+                assert same(got, ref), (shape, model, i, used)
+
+
+def test_march_refusals():
+    def refused(spec, shape, storage="f32", **plan):
+        g = rd.Grid(shape, spec.ns, spec.h, storage)
+        g.set_model(spec)
+        with pytest.raises(rd.RDError) as e:
+            g.set_plan(**plan)
+        assert e.value.code == rd.EINVAL
+        g.step(1)
+        g.close()
+
+    p = dict(kernel="march", vx=4, ry=1, waves=8, prefetch=2)
+    mirror = FACES["mirror"]
+    refused(spec_of("diffusion", (8, 8, 64), (HELD, MIRROR, MIRROR, MIRROR)), (8, 8, 64), **p)
+    refused(spec_of("diffusion", (8, 8, 64), (MIRROR, MIRROR, GHOST, MIRROR)), (8, 8, 64), **p)
+    refused(spec_of("diffusion", (8, 8, 64), mirror), (8, 8, 64), **dict(p, vx=2))
+    refused(spec_of("diffusion", (8, 8, 64), mirror), (8, 8, 64), **dict(p, prefetch=5))
+    refused(spec_of("diffusion", (1, 8, 64), mirror), (1, 8, 64), **p)      # fewer planes than steps
+    refused(spec_of("diffusion", (8, 8, 20), mirror), (8, 8, 20), **p)      # rows of fewer lanes than a tile takes
+    refused(spec_of("diffusion", (8, 8, 64), mirror), (8, 8, 64), "f16", **p)
+    rk = spec_of("diffusion", (8, 8, 64), mirror)
+    rk.integrator = "rk2"
+    refused(rk, (8, 8, 64), **p)
+    # a plan asked for by name has to take a rounding that is set later
+    spec = spec_of("brusselator", (8, 8, 64), mirror)
+    g = rd.Grid((8, 8, 64), 2, spec.h, "bf16")
+    g.set_model(spec)
+    g.set_plan(**p)
+    with pytest.raises(rd.RDError):
+        g.set_rounding("stochastic", 1)
+    g.set_plan()
+    g.set_rounding("stochastic", 1)
+    g.step(3)
+    assert g.plan()["kernel"] != 8
+    g.set_rounding("nearest")
+    assert g.plan()["kernel"] == 8
+    g.close()
