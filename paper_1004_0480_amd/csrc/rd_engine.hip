@@ -41,6 +41,14 @@ int fail(int code, const std::string& msg) {
             return fail(RD_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_));     \
     } while (0)
 
+// Field buffers start at different places of the memory's interleave (17 units
+// of 256 bytes apart), so that the streams of a step, which run through all
+// fields at the same cells, do not meet in the same channels (front 384x384x512
+// FP32, six streams: 391 us a step with buffers at equal offsets, 374 so; with
+// 64 KB, 1 MB or 2 MB more between them the same).
+constexpr size_t kStagger = 17 * 256;
+size_t stagger_bytes(int buffer) { return size_t(buffer) * kStagger; }
+
 size_t elem_size(int storage) { return storage == RD_F32 ? 4 : 2; }
 int pitch_of(int64_t nx) { return int((nx + 63) / 64 * 64); }
 size_t field_elems(int64_t nx, int64_t ny, int64_t nz) {
@@ -250,6 +258,7 @@ struct rd_grid {
     long long plane = 0;
     size_t elems = 0;
     void* buf[2][RD_MAX_SPECIES] = {};
+    void* mem[2][RD_MAX_SPECIES] = {}; // their allocations (see kStagger)
     float* aux = nullptr;              // Cahn-Hilliard mu (FP32)
     int cur = 0;                       // buffer parity holding the current state
     bool has_model = false;
@@ -999,6 +1008,7 @@ extern "C" size_t rd_grid_bytes(int64_t nx, int64_t ny, int64_t nz, int32_t nspe
     if (storage_dtype != RD_F32 && storage_dtype != RD_BF16 && storage_dtype != RD_F16) return 0;
     const size_t e = field_elems(nx, ny, nz);
     size_t b = 2 * size_t(nspecies) * e * elem_size(storage_dtype);
+    for (int i = 0; i < 2 * nspecies; ++i) b += stagger_bytes(i);
     if (with_aux) b += e * sizeof(float);
     b += 12 * sizeof(StepArgs) + 2 * sizeof(StepClock) + 2 * kRedBlocks * sizeof(double) + 2 * sizeof(double);
     return b;
@@ -1142,12 +1152,14 @@ extern "C" int rd_create_grid(int64_t nx, int64_t ny, int64_t nz, int32_t nspeci
     };
     for (int p = 0; p < 2; ++p)
         for (int s = 0; s < nspecies; ++s) {
-            const hipError_t e = hipMalloc(&g->buf[p][s], bytes);
+            const size_t off = stagger_bytes(p * nspecies + s);
+            const hipError_t e = hipMalloc(&g->mem[p][s], bytes + off);
             if (e != hipSuccess) {
-                g->buf[p][s] = nullptr;
+                g->mem[p][s] = nullptr;
                 return cleanup(e == hipErrorOutOfMemory ? RD_ENOMEM : RD_EDEVICE,
                                std::string("hipMalloc: ") + hipGetErrorString(e));
             }
+            g->buf[p][s] = static_cast<char*>(g->mem[p][s]) + off;
             if (hipMemsetAsync(g->buf[p][s], 0, bytes, g->stream) != hipSuccess)
                 return cleanup(RD_EDEVICE, "hipMemsetAsync failed");
         }
@@ -1167,7 +1179,7 @@ extern "C" int rd_destroy_grid(rd_grid* g) {
     if (g->batch) rd_batch_remove(g->batch, g);
     (void)hipStreamSynchronize(g->stream);
     drop_graphs(g);
-    for (auto& row : g->buf)
+    for (auto& row : g->mem)
         for (auto& b : row) (void)hipFree(b);
     for (auto& b : g->stage) (void)hipFree(b);
     (void)hipFree(g->aux);
