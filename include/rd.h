@@ -207,12 +207,16 @@ typedef struct rd_plan {
     int32_t vx;           /* TILED/BLOCK: cells per lane along x (1, 2 or 4);
                              LDS: 4 (rows of <= 256 cells) or 8 (257..512);
                              LDS2: 4 (rows of 256 cells) or 8 (of 512);
-                             FUSED: waves computing the chemical potential;
+                             FUSED: waves computing the chemical potential,
+                             or 0: the register-march form, every wave computing
+                             both (FP32 or BF16, forward Euler; mirror faces, A
+                             and B also held or ghost z faces, no Fickian term of
+                             C; stochastic rounding for nx a multiple of 4);
                              MARCH: 4 (cells per lane);
                              TRING: 2 (cells per lane)                         */
     int32_t ry;           /* TILED/BLOCK: rows per wave (1, 2 or 4);
                              LDS/LDS2/FUSED/TRING: rows per workgroup;
-                             MARCH: rows per lane (1 or 2)                     */
+                             MARCH, FUSED with vx 0: rows per lane (1 or 2)    */
     int32_t waves;        /* TILED/BLOCK: waves per workgroup (1 or 4);
                              LDS/LDS2: computing waves (plus one loading wave);
                              FUSED: waves updating the fields (plus vx waves
@@ -220,13 +224,13 @@ typedef struct rd_plan {
                              TRING: computing waves (plus one loading wave, or
                              two when the fields' ring rows times prefetch-3
                              exceed 63 loads);
-                             MARCH: waves per workgroup                        */
+                             MARCH, FUSED with vx 0: waves per workgroup       */
     int32_t cz;           /* TILED/LDS/LDS2/FUSED/TRING/MARCH: z planes per workgroup, 0 = all;
                              BLOCK: planes per slab (2, 4 or 8)                */
     int32_t prefetch;     /* TILED: planes in flight ahead of the z window (1-2);
                              LDS/LDS2/FUSED/TRING: input ring slots;
                              MARCH: time steps per launch (2 to 4; the rest of a
-                             count in launches of two and one)                 */
+                             count in launches of two and one); FUSED with vx 0: 1 */
     int32_t order;        /* BLOCK/LDS/LDS2/FUSED/TRING/MARCH: tile enumeration, 0 = x, then y, then z chunk;
                              1 = z chunk fastest (z-neighbour slabs run together
                              on one XCD and share its L2)                       */

@@ -182,6 +182,21 @@ hipError_t launch_march(int storage, int pm, int cfg, int k, int variant, const 
     }
 }
 
+hipError_t launch_fmarch(int storage, int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks,
+                         hipStream_t s) {
+    switch (storage) {
+    case ST_F32: return launch_fmarch_f32(cfg, cd, sr, ragged, d, blocks, s);
+    case ST_BF16: return launch_fmarch_bf16(cfg, cd, sr, ragged, d, blocks, s);
+    default: return hipErrorNotSupported;
+    }
+}
+
+int fmarch_cfg_index(int ry, int w) {
+    for (int i = 0; i < kNumFmarchCfgs; ++i)
+        if (kFmarchCfgs[i].ry == ry && kFmarchCfgs[i].w == w) return i;
+    return -1;
+}
+
 int march_cfg_index(int ry, int w, int k) {
     for (int i = 0; i < kNumMarchCfgs; ++i)
         if (kMarchCfgs[i].ry == ry && kMarchCfgs[i].w == w && kMarchCfgs[i].k == k) return i;
@@ -359,6 +374,20 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
     return best;
 }
 
+// The one-pass front plan in its register-march form.
+bool is_fmarch(const rd_plan& p) { return p.kernel == RD_KERNEL_FUSED && p.vx == 0; }
+
+constexpr int kFrontHalo = 2;   // rows a tile of the front kernel loses on each side
+
+// The faces the register-march front kernel takes: mirror for C, and along x
+// and y for A and B, whose z faces may also be held or fixed ghosts.
+bool fmarch_axes(const StepArgs& a) {
+    for (int f = 0; f < 3; ++f)
+        for (int k = 0; k < 6; ++k)
+            if (f < 2 && k >= 4 ? a.bck[f][k] == BC_PERIODIC : a.bck[f][k] != BC_MIRROR) return false;
+    return true;
+}
+
 // Predicted time of one launch of a register march, in microseconds: the
 // workgroups a CU holds, in rounds, each plane of a round taking the vector
 // issue of the CU's workgroups or, where that is less, a plane's latency (loads,
@@ -411,6 +440,23 @@ double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, in
     return march_cost(k, c.ry, c.w, m, nx, ny, nz, cz);
 }
 
+// The front kernel: a fit to 14 grids from 64^3 to 384x384x512 (FP32 and BF16),
+// 11 % off on average, its plans within 3 % of the best measured.
+double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz,
+                   int cz) {
+    const int t = 64 * c.w;
+    MarchCost k{};
+    k.instr = 70.7 * (storage == ST_F32 ? 1.0 : 1.035) * (sr ? 1.6 : 1.0);   // (the generator's calls)
+    k.latency = 1.22, k.launch = 1.02, k.fill = 1.38;
+    k.tbs = 5.09, k.halo_xy = 0.33, k.halo_z = 1.1;
+    k.halo = kFrontHalo;
+    k.extra = 2;
+    k.cell_bytes = 3 * double(elem_size(storage));
+    k.lds = 2LL * 4 * 16 * (c.ry == 1 ? 1 : 2) * t + 2LL * 2 * 16 * (c.w + t / kMarchMinLanes) * c.ry;
+    k.vgprs = c.ry == 1 ? 112 : 192;
+    return march_cost(k, c.ry, c.w, m, nx, ny, nz, cz);
+}
+
 bool march_axes(const StepArgs& a, int nf) {
     // the fields of a pass share their face rules: mirror or periodic along y
     // and z, and mirror, periodic or a fixed ghost value along x
@@ -426,13 +472,14 @@ bool march_axes(const StepArgs& a, int nf) {
 
 // Decomposition of a tiled plan: fills tiles_* / cz, returns workgroups.
 long long set_tiling(StepArgs& a, const rd_plan& p, int storage = ST_F32, int pm = -1) {
-    if (p.kernel == RD_KERNEL_MARCH) {
+    const bool front = is_fmarch(p);
+    if (p.kernel == RD_KERNEL_MARCH || front) {
         const MarchGeom g = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC,
-                                       {p.ry, p.waves, p.prefetch});
+                                       {p.ry, p.waves, front ? kFrontHalo : p.prefetch});
         a.mg[MG_LANES] = g.l;
         a.mg[MG_HALO] = g.halo;
         a.mg[MG_STEPS] = p.prefetch;
-        if (pm >= 0) {
+        if (pm >= 0 && !front) {
             // launches of one step: their own chunk length of least predicted time
             MarchGeom g1 = g;
             g1.by = g.by1;
@@ -515,6 +562,33 @@ int balanced_cz_k(const rd_grid* g, long long tiles, int k) {
         }
     }
     return best;
+}
+
+// The same for the front kernel.
+bool fmarch_plan(const rd_grid* g, int shape, rd_plan* out) {
+    double best = 1e300;
+    for (int i = 0; i < kNumFmarchCfgs; ++i) {
+        if (shape >= 0 && i != shape) continue;
+        const FmarchCfg c = kFmarchCfgs[i];
+        rd_plan p{};
+        p.kernel = RD_KERNEL_FUSED;
+        p.ry = c.ry;
+        p.waves = c.w;
+        p.prefetch = 1;
+        int cfg = -1;
+        if (check_plan(g, p, &cfg) != RD_OK) continue;
+        const StepArgs& a = g->args[0][1];
+        const MarchGeom m = march_geom(a.nx, a.ny, false, {c.ry, c.w, kFrontHalo});
+        for (int n = 1; n <= 64 && n <= g->nz; ++n) {
+            p.cz = int((g->nz + n - 1) / n);
+            const double us = fmarch_time(g->storage, a.sr != 0, c, m, g->nx, g->ny, g->nz, p.cz);
+            if (us < best) {
+                best = us;
+                *out = p;
+            }
+        }
+    }
+    return best < 1e300;
 }
 
 // z chunk lengths the autotuner tries: the predicted one and those that fill
@@ -602,6 +676,26 @@ rd_plan heuristic_plan(const rd_grid* g) {
     // against 44, pollutant 512x512x128 171 against 218, diffusion 64^3 2.5
     // against 6.1).
     if (g->model != RD_MODEL_FRONT_CH && march_plan(g, -1, &best)) return best;
+    // and its front form, against the one-pass LDS form this rule chose before
+    // (us per step: 384x384x512 FP32 376 against 420, BF16 232 against 383;
+    // 248x200x180 42 against 62 and 29 against 65; 64^3 8.4 against 26)
+    if (g->model == RD_MODEL_FRONT_CH && fmarch_plan(g, -1, &best)) return best;
+    if (g->model == RD_MODEL_FRONT_CH && !g->args[0][0].s19) {
+        // the one-pass front kernel, its largest shape for this storage
+        for (int i = 0; i < kNumFchCfgs; ++i) {
+            if (!fch_ok(g->storage, i)) continue;
+            rd_plan p{};
+            p.kernel = RD_KERNEL_FUSED;
+            p.vx = kFchCfgs[i].wm;
+            p.ry = kFchCfgs[i].by;
+            p.waves = kFchCfgs[i].wu;
+            p.prefetch = kFchCfgs[i].d;
+            const long long tiles = ((g->nx + kFchTile - 1) / kFchTile) * ((g->ny + p.ry - 1) / p.ry);
+            p.cz = balanced_cz(g, tiles);
+            int cfg = -1;
+            if (check_plan(g, p, &cfg) == RD_OK) return p;
+        }
+    }
     if (g->args[0][0].s19) {
         // 19-point: the first LDS-ring shape this grid and model take, with
         // z chunks that give about two workgroups per CU; else direct
@@ -665,6 +759,27 @@ int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
             if (!lds_ok(g->storage, g->pass_pm[k], cfg))
                 return fail(RD_EINVAL, "LDS ring shape not compiled for this model and storage");
         if (p.cz < 0) return fail(RD_EINVAL, "cz must be >= 0");
+        *cfg_out = cfg;
+        return RD_OK;
+    }
+    if (is_fmarch(p)) {
+        const int cfg = p.prefetch == 1 ? fmarch_cfg_index(p.ry, p.waves) : -1;
+        if (cfg < 0 || !fmarch_ok(g->storage, cfg))
+            return fail(RD_EINVAL, "one-pass front shape not available");
+        if (g->model != RD_MODEL_FRONT_CH || g->args[0][0].s19)
+            return fail(RD_EINVAL, "the one-pass plan takes the 7-point front model only");
+        const StepArgs& a = g->args[0][1];
+        if (g->integrator >= RD_RK2 || (g->sr_mode != RD_ROUND_NEAREST && a.nx % kMarchVX != 0))
+            return fail(RD_EINVAL, "the register-march front plan takes forward Euler, and stochastic rounding of "
+                                   "rows of a multiple of 4 cells");
+        if (p.cz < 0) return fail(RD_EINVAL, "cz must be >= 0");
+        if (g->ny < 2 || g->nz < 2 || g->plane * int64_t(elem_size(g->storage)) >= (1LL << 31))
+            return fail(RD_EINVAL, "grid too small or its planes too large for the register march");
+        if (!fmarch_axes(a) || a.kx[2] != 0.f || a.ky[2] != 0.f || a.kz[2] != 0.f)
+            return fail(RD_EINVAL, "the register-march front plan takes mirror faces (A and B also held or ghost "
+                                   "z faces) and a C without a Fickian term");
+        if (march_geom(a.nx, a.ny, false, {p.ry, p.waves, kFrontHalo}).l == 0)
+            return fail(RD_EINVAL, "the register march has no tile for this grid");
         *cfg_out = cfg;
         return RD_OK;
     }
@@ -838,7 +953,12 @@ int launch_march_steps(rd_grid* g, int parity, int steps) {
 int launch_one_step(rd_grid* g, int parity) {
     if (g->eff.kernel == RD_KERNEL_MARCH) return launch_march_steps(g, parity, g->eff.prefetch);
     if (one_pass(g)) {
-        const hipError_t e = launch_fch(g->storage, g->cfg, g->args[parity][1], g->d_args + parity * 2 + 1,
+        const StepArgs& a = g->args[parity][1];
+        const hipError_t e =
+            is_fmarch(g->eff)
+                ? launch_fmarch(g->storage, g->cfg, a.p[5] != 0.f, a.sr != 0, a.nx % kMarchVX != 0,
+                                g->d_args + parity * 2 + 1, g->blocks[1], g->stream)
+                : launch_fch(g->storage, g->cfg, g->args[parity][1], g->d_args + parity * 2 + 1,
                                         g->blocks[1], g->stream);
         if (e != hipSuccess) return fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
         return RD_OK;
@@ -1449,7 +1569,7 @@ extern "C" int rd_set_rounding(rd_grid* g, int32_t mode, uint64_t seed) {
     if (mode == RD_ROUND_STOCHASTIC && g->has_model && g->integrator >= RD_RK2)
         return fail(RD_EINVAL, "stochastic rounding takes forward Euler steps");
     RD_HIP(hipStreamSynchronize(g->stream));
-    if (g->has_model && g->plan.kernel == RD_KERNEL_MARCH) {
+    if (g->has_model && (g->plan.kernel == RD_KERNEL_MARCH || is_fmarch(g->plan))) {
         // a plan asked for by name has to take the rounding
         const int old = g->sr_mode;
         int cfg = -1;
@@ -1803,6 +1923,15 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
         if (!march_plan(g, i, &p)) continue;
         const StepArgs& a = g->args[0][0];
         const MarchGeom m = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, kMarchCfgs[i]);
+        for (int cz : march_chunks(g, m, p.cz)) {
+            p.cz = cz;
+            cands.push_back(p);
+        }
+    }
+    for (int i = 0; i < kNumFmarchCfgs && !g->args[0][0].s19 && g->model == RD_MODEL_FRONT_CH; ++i) {
+        rd_plan p{};
+        if (!fmarch_plan(g, i, &p)) continue;
+        const MarchGeom m = march_geom(int(g->nx), int(g->ny), false, {p.ry, p.waves, kFrontHalo});
         for (int cz : march_chunks(g, m, p.cz)) {
             p.cz = cz;
             cands.push_back(p);

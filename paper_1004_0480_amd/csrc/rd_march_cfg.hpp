@@ -55,6 +55,22 @@ constexpr bool march_ok(int storage, int pm, int i) {
     return (nf == 1 ? c.ry == 1 : nf == 2 && c.k == 2) && march_lds_bytes(nf, i) <= 160 * 1024;
 }
 
+// Shapes of the register-march front kernel (rd_fmarch.hpp): rows per lane,
+// waves per workgroup.  One step per launch; its tiles lose two rows on each
+// side, as those of two steps of the others do (mu, then its Laplacian).
+struct FmarchCfg { int ry, w; };
+constexpr FmarchCfg kFmarchCfgs[] = {{2, 8}, {1, 8}, {1, 16}};
+constexpr int kNumFmarchCfgs = sizeof(kFmarchCfgs) / sizeof(kFmarchCfgs[0]);
+constexpr bool fmarch_ok(int storage, int i) {
+    return (storage == ST_F32 || storage == ST_BF16) && i >= 0 && i < kNumFmarchCfgs;
+}
+// Variants: C with a redissolution term, stochastic rounding, rows that end
+// inside a lane.
+hipError_t launch_fmarch(int storage, int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks,
+                         hipStream_t s);
+hipError_t launch_fmarch_f32(int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
+hipError_t launch_fmarch_bf16(int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
+
 // The lane exchange a geometry needs: none (rows lie inside a wave and end at
 // whole lanes), through LDS, or through LDS with a last lane that is not full.
 // MARCH_MIRROR is added where both x faces are mirrors.

@@ -120,6 +120,28 @@ def test_default_plan_bitwise(storage):
                 assert same(got, ref), (shape, model, i, used)
 
 
+@pytest.mark.parametrize("storage,rounding", [("f32", None), ("bf16", None), ("bf16", 5)])
+def test_front_march_bitwise(storage, rounding):
+    for shape in SHAPES + [(2, 9, 388), (3, 64, 32)]:
+        for za, zb, k2 in ((HELD, MIRROR, 0.0), (MIRROR, GHOST, 0.5), (GHOST, HELD, 0.0)):
+            spec = W.front_spec()
+            spec.params = dict(spec.params, k2=k2)
+            spec.bc[0][4], spec.bc[1][5] = za, zb
+            f = [0.5 * x for x in fields_of(shape, 3, 6)]
+            ref, _ = run(spec, shape, f, storage, [3], dict(kernel="direct"), rounding=rounding)
+            for ry, w in ((2, 8), (1, 8), (1, 16)):
+                for cz in (0, 3):
+                    plan = dict(kernel="fused", vx=0, ry=ry, waves=w, prefetch=1, cz=cz)
+                    if rounding is not None and shape[2] % 4:
+                        with pytest.raises(rd.RDError):
+                            run(spec, shape, f, storage, [1], plan, rounding=rounding)
+                        continue
+                    got, _ = run(spec, shape, f, storage, [3], plan, rounding=rounding)
+                    assert same(got, ref), (shape, za, zb, plan)
+            got, _ = run(spec, shape, f, storage, [3], rounding=rounding)
+            assert same(got, ref), (shape, za, zb, "default plan")
+
+
 def test_march_refusals():
     def refused(spec, shape, storage="f32", **plan):
         g = rd.Grid(shape, spec.ns, spec.h, storage)
