@@ -182,6 +182,19 @@ hipError_t launch_march(int storage, int pm, int cfg, int k, int variant, const 
     }
 }
 
+hipError_t launch_batched_march(int storage, const int* meta, const BatchEntry* ents, int launch, int blocks,
+                                hipStream_t s) {
+    switch (storage) {
+    case ST_F32: return launch_batched_march_f32(meta, ents, launch, blocks, s);
+    case ST_BF16: return launch_batched_march_bf16(meta, ents, launch, blocks, s);
+    default: return hipErrorNotSupported;
+    }
+}
+
+int batched_march_blocks_per_cu(int storage) {
+    return storage == ST_F32 ? batched_march_blocks_per_cu_f32() : batched_march_blocks_per_cu_bf16();
+}
+
 hipError_t launch_fmarch(int storage, int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks,
                          hipStream_t s) {
     switch (storage) {
@@ -468,6 +481,14 @@ bool march_axes(const StepArgs& a, int nf) {
         if (a.bck[f][2] != a.bck[f][3] || a.bck[f][4] != a.bck[f][5]) return false;
     }
     return true;
+}
+
+// The lane exchange of a tiled grid.
+int march_variant(const StepArgs& a) {
+    const int l = a.mg[MG_LANES];
+    const bool whole_periodic = a.bck[0][0] == BC_PERIODIC && a.mg[MG_HALO] == 0;
+    return a.nx % kMarchVX != 0 ? MARCH_RAGGED
+           : 64 % l != 0 || (whole_periodic && l != 64) ? MARCH_EDGES : MARCH_PLAIN;
 }
 
 // Decomposition of a tiled plan: fills tiles_* / cz, returns workgroups.
@@ -887,8 +908,7 @@ int apply_plan(rd_grid* g) {
                     const bool per = a.bck[0][0] == BC_PERIODIC;
                     const MarchGeom mg = march_geom(a.nx, a.ny, per, kMarchCfgs[cfg]);
                     g->march_rows = mg.by + 2 * p.prefetch;
-                    g->variant = a.nx % kMarchVX != 0 ? MARCH_RAGGED
-                                 : 64 % mg.l != 0 || (per && mg.halo == 0 && mg.l != 64) ? MARCH_EDGES : MARCH_PLAIN;
+                    g->variant = march_variant(a);
                     if (a.bck[0][0] == BC_MIRROR && a.bck[0][1] == BC_MIRROR) g->variant |= MARCH_MIRROR;
                 }
                 (void)set_tiling(g->rk_args[par][k], p);
@@ -2069,6 +2089,7 @@ struct Member {
     rd_grid* g;
     int64_t steps_left;
     size_t bytes;
+    int march_tiles; // xy tiles of the batched register march (0: not a grid it takes)
 };
 }  // namespace
 
@@ -2088,8 +2109,9 @@ struct rd_batch {
     size_t tab_bytes = 0;
     hipEvent_t tab_done[2] = {nullptr, nullptr};
     bool tab_pending[2] = {false, false};
-    std::map<int64_t, hipGraphExec_t> graphs;   // by chunk
+    std::map<std::pair<int64_t, bool>, hipGraphExec_t> graphs;   // by steps and kernel
     int blocks = 0;
+    int march_blocks = 0;          // register march (0: not for this storage)
 };
 
 namespace {
@@ -2098,6 +2120,41 @@ namespace {
 size_t meta_bytes(int max_grids) { return (size_t(max_grids + 5) * sizeof(int) + 255) / 256 * 256; }
 size_t table_bytes(int max_grids, int n) { return meta_bytes(max_grids) + size_t(std::max(n, 1)) * sizeof(BatchEntry); }
 }
+
+namespace {
+// xy tiles of a grid in the batched register march, 0 if its faces, rows or
+// planes are none the march's two-step shapes take (see check_plan).
+int batch_march_tiles(const rd_grid* g) {
+    const StepArgs& a = g->args[0][0];
+    if (g->ny < 2 || g->nz < 2 || g->plane * int64_t(elem_size(g->storage)) >= (1LL << 31) ||
+        !march_axes(a, march_fields(g->pass_pm[0])))
+        return 0;
+    const MarchGeom m = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, {kBatchMarch.ry, kBatchMarch.w, 2});
+    return m.l == 0 ? 0 : int(m.tx * ((g->ny + m.by - 1) / m.by));
+}
+
+// z planes per item of a tick: the fewest planes marched per workgroup slot,
+// plus half an item for the end of a launch, where the slots run dry one by
+// one.  An item marches four planes more than its chunk (the halo and the
+// start), so short chunks pay when few grids are left.
+int batch_march_chunk(const std::vector<Member>& members, int slots) {
+    int best = 32;
+    double best_t = 1e300;
+    for (int cz : {4, 6, 8, 12, 16, 24, 32, 48}) {
+        double planes = 0.0;
+        for (const Member& m : members) {
+            const int c = int(std::min<int64_t>(cz, m.g->nz));
+            planes += (m.g->model == RD_MODEL_BRUSSELATOR ? 2.0 : 1.0) * m.march_tiles * ((m.g->nz + c - 1) / c) * (c + 4);
+        }
+        const double t = planes / slots + 0.5 * (cz + 4);
+        if (t < best_t) {
+            best_t = t;
+            best = cz;
+        }
+    }
+    return best;
+}
+}  // namespace
 
 extern "C" int rd_batch_create(int32_t max_grids, size_t hbm_budget_bytes, int32_t storage_dtype,
                                void* hip_stream, rd_batch** out) {
@@ -2121,6 +2178,7 @@ extern "C" int rd_batch_create(int32_t max_grids, size_t hbm_budget_bytes, int32
         return fail(RD_ENOMEM, "batch table allocation failed");
     }
     b->blocks = batched_blocks_per_cu(storage_dtype) * num_cus();
+    if (storage_dtype != RD_F16) b->march_blocks = batched_march_blocks_per_cu(storage_dtype) * num_cus();
     *out = b;
     return RD_OK;
 }
@@ -2155,7 +2213,7 @@ extern "C" int rd_batch_add(rd_batch* b, rd_grid* g, int64_t steps) {
     const size_t gb = rd_grid_bytes(g->nx, g->ny, g->nz, g->ns, g->storage, 0);
     if (b->bytes + gb > b->budget) return fail(RD_ENOMEM, "grid would exceed the batch's HBM budget");
     RD_HIP(hipStreamSynchronize(g->stream));
-    b->members.push_back({g, steps, gb});
+    b->members.push_back({g, steps, gb, b->march_blocks > 0 ? batch_march_tiles(g) : 0});
     b->bytes += gb;
     g->batch = b;
     return RD_OK;
@@ -2205,17 +2263,26 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
     int* meta = reinterpret_cast<int*>(h_tab);
     BatchEntry* ents = reinterpret_cast<BatchEntry*>(h_tab + moff);
     std::memset(h_tab, 0, table_bytes(b->max_grids, ng));
+    long long items = 0;
+    int64_t max_steps = 0;
+    // two steps a launch where every member's grid allows, else one a launch
+    bool march = true;
+    for (const Member& m : b->members) {
+        max_steps = std::max(max_steps, m.steps_left);
+        march = march && m.march_tiles > 0;
+    }
+    const int64_t run = std::min(chunk, max_steps);
+    const int march_cz = march ? batch_march_chunk(b->members, b->march_blocks) : 0;
     std::vector<int> order(static_cast<size_t>(ng));
     for (int i = 0; i < ng; ++i) order[size_t(i)] = i;
     auto tile_cost = [&](int i) {
         const rd_grid* g = b->members[size_t(i)].g;
         const long long fields = g->model == RD_MODEL_BRUSSELATOR ? 2 : 1;
+        if (march) return fields * std::min<long long>(g->nz, march_cz);
         return fields * std::min<long long>(g->nx, kTrTile) * std::min<long long>(g->ny, kBatchTr.by) *
                std::min<long long>(g->nz, kBatchTr.cz);
     };
     std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return tile_cost(p) > tile_cost(q); });
-    long long items = 0;
-    int64_t max_steps = 0;
     for (int i = 0; i < ng; ++i) {
         const Member& m = b->members[size_t(order[size_t(i)])];
         BatchEntry& e = ents[i];
@@ -2228,17 +2295,25 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
         tile.waves = kBatchTr.wc;
         tile.prefetch = kBatchTr.d;
         tile.cz = kBatchTr.cz;
+        if (march) {
+            tile.kernel = RD_KERNEL_MARCH;
+            tile.vx = kMarchVX;
+            tile.ry = kBatchMarch.ry;
+            tile.waves = kBatchMarch.w;
+            tile.prefetch = 2;
+            tile.cz = march_cz;
+        }
         for (int par = 0; par < 2; ++par) {
             e.args[par] = m.g->args[par][0];
             e.ntiles = int(set_tiling(e.args[par], tile));
+            if (march) e.args[par].mg[MG_VARIANT] = march_variant(e.args[par]);
         }
         e.model = m.g->model == RD_MODEL_BRUSSELATOR ? 1 : 0;
         e.first_item = int(items);
         meta[4 + i] = int(items);
         e.parity = m.g->cur;
-        e.steps_left = m.steps_left;
+        e.steps_left = march ? std::min(m.steps_left, run) : m.steps_left;
         items += e.ntiles;
-        max_steps = std::max(max_steps, m.steps_left);
     }
     if (items > 0x7fffffffLL) return fail(RD_EINVAL, "batch work list too long");
     meta[0] = ng;
@@ -2250,16 +2325,20 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
     RD_HIP(hipEventRecord(b->tab_done[tb], b->stream));
     b->tab_pending[tb] = true;
     b->next_tab = tb ^ 1;
-    const int64_t run = std::min(chunk, max_steps);
+    const int64_t launches = march ? (run + 1) / 2 : run;
+    auto launch = [&](int64_t i) {
+        int* tab = reinterpret_cast<int*>(b->d_tab);
+        const BatchEntry* en = reinterpret_cast<const BatchEntry*>(b->d_tab + meta_bytes(b->max_grids));
+        return march ? launch_batched_march(b->storage, tab, en, int(i), b->march_blocks, b->stream)
+                     : launch_batched(b->storage, tab, en, int(i), b->blocks, b->stream);
+    };
     if (b->stream != nullptr) {
-        auto it = b->graphs.find(run);
+        const std::pair<int64_t, bool> key{launches, march};
+        auto it = b->graphs.find(key);
         if (it == b->graphs.end()) {
             RD_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
             hipError_t le = hipSuccess;
-            for (int64_t i = 0; i < run && le == hipSuccess; ++i)
-                le = launch_batched(b->storage, reinterpret_cast<int*>(b->d_tab),
-                                    reinterpret_cast<const BatchEntry*>(b->d_tab + meta_bytes(b->max_grids)),
-                                    int(i), b->blocks, b->stream);
+            for (int64_t i = 0; i < launches && le == hipSuccess; ++i) le = launch(i);
             hipGraph_t graph = nullptr;
             const hipError_t ce = hipStreamEndCapture(b->stream, &graph);
             if (le != hipSuccess || ce != hipSuccess) {
@@ -2270,14 +2349,12 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
             const hipError_t ie = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
             (void)hipGraphDestroy(graph);
             if (ie != hipSuccess) return fail(RD_EDEVICE, std::string("batch instantiate: ") + hipGetErrorString(ie));
-            it = b->graphs.emplace(run, ex).first;
+            it = b->graphs.emplace(key, ex).first;
         }
         RD_HIP(hipGraphLaunch(it->second, b->stream));
     } else {
-        for (int64_t i = 0; i < run; ++i) {
-            const hipError_t le = launch_batched(b->storage, reinterpret_cast<int*>(b->d_tab),
-                                                 reinterpret_cast<const BatchEntry*>(b->d_tab + meta_bytes(b->max_grids)),
-                                                 int(i), b->blocks, b->stream);
+        for (int64_t i = 0; i < launches; ++i) {
+            const hipError_t le = launch(i);
             if (le != hipSuccess) return fail(RD_EDEVICE, std::string("batch launch: ") + hipGetErrorString(le));
         }
     }
@@ -2285,7 +2362,7 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
     std::vector<Member> keep;
     for (auto& m : b->members) {
         const int64_t done = std::min(run, m.steps_left);
-        m.g->cur ^= int(done & 1);
+        m.g->cur ^= int((march ? (done + 1) / 2 : done) & 1);   // every launch swaps the buffers
         m.steps_left -= done;
         if (m.steps_left == 0) {
             finished[(*n_finished)++] = m.g;

@@ -155,42 +155,33 @@ template <int NF> struct MarchConst {
     }
 };
 
-template <class M, class S, int RY, int W, int K, bool XEX, bool RAG, bool MIR>
-__global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restrict__ pa) {
-    constexpr int NF = M::NF, T = 64 * W, ES = int(sizeof(typename S::T));
-    static_assert(M::NO == NF, "every field is stored");
-    constexpr int NR = RY == 1 ? 1 : 2;              // boundary rows of a lane
-    constexpr int NE = K * NF;                        // values of an edge slot: by level, then field
-    constexpr int NX = (W + T / kMarchMinLanes) * RY + 1;   // edge slots of one side, the last the face values
-    __shared__ __attribute__((aligned(16))) float rows_s[2 * K * NF * NR * T * 4];
-    __shared__ __attribute__((aligned(16))) float edge_s[2 * 2 * NX * NE];
+// LDS of a march of NF fields and K levels, in floats: the boundary rows of
+// every thread and the edge cells, each twice (by parity).
+template <int NF, int RY, int W, int K>
+struct MarchLds {
+    static constexpr int T = 64 * W;
+    static constexpr int NR = RY == 1 ? 1 : 2;       // boundary rows of a lane
+    static constexpr int NE = K * NF;                // values of an edge slot: by level, then field
+    static constexpr int NX = (W + T / kMarchMinLanes) * RY + 1;   // edge slots of one side, the last the face values
+    static constexpr int ROWS = 2 * K * NF * NR * T * 4, EDGES = 2 * 2 * NX * NE;
+};
+
+// One workgroup's march: K steps of planes z0 .. z1-1 of the rows stored from
+// yb on (a tile leaves KG rows on each side, KG >= K) in x tile tx.
+template <class M, class S, int RY, int W, int K, int KG, bool XEX, int RAG, bool MIR>
+__device__ __forceinline__ void march_tile_steps(const StepArgs& a, RD_LDS float* rows_l, RD_LDS float* edge_l, int tx,
+                                                 int yb, int z0, int z1) {
 #ifdef __HIP_DEVICE_COMPILE__
-    const StepArgs& a = *pa;
-    RD_LDS float* rows_l = (RD_LDS float*)&rows_s[0];
-    RD_LDS float* edge_l = (RD_LDS float*)&edge_s[0];
+    using R = MarchLds<M::NF, RY, W, K>;
+    constexpr int NF = M::NF, T = R::T, ES = int(sizeof(typename S::T));
+    constexpr int NR = R::NR, NE = R::NE, NX = R::NX;
+    static_assert(M::NO == NF && KG >= K, "every field is stored, from a tile that is deep enough");
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
 
     // ---- the tile ---------------------------------------------------------
     const int L = a.mg[MG_LANES], halo = a.mg[MG_HALO], G = T / L;
-    const int BY = G * RY - 2 * K;                   // rows stored
-    const bool left_over = a.mg[MG_STEPS] != K;
-    const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz, chunks = left_over ? a.mg[MG_LEFT_CHUNKS] : a.chunks_z;
-    const int tiles_y = (a.ny + BY - 1) / BY;
-    int b = xcd_tile(blockIdx.x, gridDim.x);
-    int tx, ty, tz;
-    if (a.zfast) {
-        tz = b % chunks;
-        b /= chunks;
-        tx = b % a.tiles_x;
-        ty = b / a.tiles_x;
-    } else {
-        tx = b % a.tiles_x;
-        b /= a.tiles_x;
-        ty = b % tiles_y;
-        tz = b / tiles_y;
-    }
-    const int yb = ty * BY, z0 = tz * cz, z1 = min(z0 + cz, a.nz);
+    const int BY = G * RY - 2 * KG;                  // rows stored
     const int yg = t / L, x4 = t - yg * L;
     const bool perx = a.bck[0][0] == BC_PERIODIC, pery = a.bck[0][2] == BC_PERIODIC,
                perz = a.bck[0][4] == BC_PERIODIC;
@@ -204,9 +195,11 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
     const bool rot = !XEX && perx;                  // rows of one wave: the lane rotation wraps them
     const bool own_l = first && a.bck[0][0] == BC_MIRROR, in_l = first && a.bck[0][0] != BC_MIRROR && !rot;
     const bool mir_r = a.bck[0][1] == BC_MIRROR;
-    const bool own_r = last && mir_r && !RAG, in_r = last && !mir_r && !RAG && !rot;
-    // RAG: the cell after the row's last, in the last lane, holds what is
-    // beyond the face
+    // the last lane is full (RAG 0: always, 1: never, 2: of any grid)
+    const bool full = RAG == 0 || (RAG == 2 && e_last == 3);
+    const bool own_r = last && mir_r && full, in_r = last && !mir_r && full && !rot;
+    // a row that ends inside its last lane: the cell after the row's last then
+    // holds what is beyond the face
     bool after[3];
 #pragma unroll
     for (int i = 1; i < 4; ++i) after[i - 1] = last && e_last + 1 == i;
@@ -216,10 +209,10 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
     int yr[M::SOURCES ? RY : 1];
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
-        const int yl = yg * RY + r, y = yb - K + yl;
-        const int ym = march_index(min(max(y, -K), a.ny - 1 + K), a.ny, pery);
+        const int yl = yg * RY + r, y = yb - KG + yl;
+        const int ym = march_index(min(max(y, -KG), a.ny - 1 + KG), a.ny, pery);
         lo[r] = unsigned(ym * a.pitch + xm) * ES;
-        so[r] = stored_x && yl >= K && yl < K + BY && y < a.ny ? unsigned(y * a.pitch + x) * ES : 0x80000000u;
+        so[r] = stored_x && yl >= KG && yl < KG + BY && y < a.ny ? unsigned(y * a.pitch + x) * ES : 0x80000000u;
         if constexpr (M::SOURCES) yr[r] = ym;
     }
 
@@ -325,9 +318,9 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
     };
     // the last cell of a row in this lane
     auto end_cell = [&](const float (&c)[4]) __attribute__((always_inline)) {
-        if constexpr (!RAG) return c[3];
+        if constexpr (RAG == 0) return c[3];
         const float ce = march_elem(e_last, c[0], c[1], c[2]);
-        return last ? ce : c[3];
+        return last && !full ? ce : c[3];
     };
     // the row ends of every level and field, one vector per slot and row
     auto export_edges = [&](int par, const float (&v0)[NF][RY][4], auto par_c) __attribute__((always_inline)) {
@@ -381,7 +374,7 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
         for (int f = 0; f < NF; ++f) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) c[f][i] = v[f][r][i];
-            if constexpr (RAG) {
+            if constexpr (RAG != 0) {
                 const float ce = march_elem(e_last, c[f][0], c[f][1], c[f][2]);
                 const float fr = MIR || mir_r ? ce : xr[f];
 #pragma unroll
@@ -395,10 +388,10 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
                 right[f] = lane_from_right_wrap(c[f][0]);
             }
             left[f] = own_l ? c[f][0] : left[f];
-            if constexpr (!RAG) right[f] = own_r ? c[f][3] : right[f];
+            if constexpr (RAG != 1) right[f] = own_r ? c[f][3] : right[f];
             if constexpr (!MIR) {
                 left[f] = in_l ? (XEX ? xl[f] : cl[f]) : left[f];
-                if constexpr (!RAG) right[f] = in_r ? (XEX ? xr[f] : cr[f]) : right[f];
+                if constexpr (RAG != 1) right[f] = in_r ? (XEX ? xr[f] : cr[f]) : right[f];
             }
         }
         int s0 = 0, s1 = 0;
@@ -519,8 +512,98 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
         plane(p + 3, std::integral_constant<int, 3>{});
     }
 #else
-    (void)pa, (void)rows_s, (void)edge_s;
+    (void)a, (void)rows_l, (void)edge_l, (void)tx, (void)yb, (void)z0, (void)z1;
 #endif
+}
+
+template <class M, class S, int RY, int W, int K, bool XEX, int RAG, bool MIR>
+__global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restrict__ pa) {
+    using R = MarchLds<M::NF, RY, W, K>;
+    __shared__ __attribute__((aligned(16))) float rows_s[R::ROWS];
+    __shared__ __attribute__((aligned(16))) float edge_s[R::EDGES];
+    const StepArgs& a = *pa;
+    const int by = R::T / a.mg[MG_LANES] * RY - 2 * K;
+    const bool left_over = a.mg[MG_STEPS] != K;
+    const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz, chunks = left_over ? a.mg[MG_LEFT_CHUNKS] : a.chunks_z;
+    const int tiles_y = (a.ny + by - 1) / by;
+    int b = xcd_tile(blockIdx.x, gridDim.x);
+    int tx, ty, tz;
+    if (a.zfast) {
+        tz = b % chunks;
+        b /= chunks;
+        tx = b % a.tiles_x;
+        ty = b / a.tiles_x;
+    } else {
+        tx = b % a.tiles_x;
+        b /= a.tiles_x;
+        ty = b % tiles_y;
+        tz = b / tiles_y;
+    }
+    const int z0 = tz * cz;
+    march_tile_steps<M, S, RY, W, K, K, XEX, RAG, MIR>(a, (RD_LDS float*)&rows_s[0], (RD_LDS float*)&edge_s[0], tx,
+                                                       ty * by, z0, min(z0 + cz, a.nz));
+}
+
+// The batched form (served grids of diffusion or the Brusselator): a persistent
+// launch walks the batch's (grid, tile) items, two steps of each grid that has
+// as many left, one of a grid with one (the same tiles).  The items are listed
+// by falling cost and dealt to the workgroups there and back (b, 2n-1-b, 2n+b,
+// ..), without a counter: claiming them from one, atomics of every workgroup on
+// one address, took longer than short items do (64 grids of 32^3 to 128^3, 20 to
+// 200 steps each, from start to end: 14.4 ms claimed, 11.4 ms dealt).  `launch`
+// counts the tick's launches.
+//
+// Against one step a launch on the tiled LDS ring (batched_tr_kernel, which
+// still takes batches with a grid this kernel does not): 22.2 -> 11.4 ms on that
+// batch, a launch of all 64 grids 150 -> 66 us a step.  Rows of short grids
+// leave a third to a half of the lanes in halos and past the grid.
+template <class S, int RY, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W / 2, W / 2))) void batched_march_kernel(
+    const int* __restrict__ meta, const BatchEntry* __restrict__ ents, int launch) {
+    using R = MarchLds<2, RY, W, 2>;                 // serves both models and both step counts
+    __shared__ __attribute__((aligned(16))) float rows_s[R::ROWS];
+    __shared__ __attribute__((aligned(16))) float edge_s[R::EDGES];
+    const int ng = meta[0];
+    const int total = meta[1];
+    const int* first = meta + 4;
+    RD_LDS float* rows_l = (RD_LDS float*)&rows_s[0];
+    RD_LDS float* edge_l = (RD_LDS float*)&edge_s[0];
+    const int n = gridDim.x, b = xcd_tile(blockIdx.x, n);
+    for (int round = 0; (long long)round * n < total; ++round) {
+        const long long item_l = (long long)round * n + (round & 1 ? n - 1 - b : b);
+        if (item_l >= total) continue;
+        const int item = int(item_l);
+        int lo = 0, hi = ng - 1;                 // last grid with first_item <= item
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (first[mid] <= item) lo = mid; else hi = mid - 1;
+        }
+        const BatchEntry& en = ents[lo];
+        const long long left = en.steps_left - 2LL * launch;
+        if (left <= 0) continue;                 // this grid already finished
+        const StepArgs& a = en.args[(en.parity + launch) & 1];
+        const TileXYZ tc = tile_coords(a, item - first[lo]);
+        const int z0 = tc.z * a.cz, z1 = min(z0 + a.cz, a.nz);
+        const int yb = tc.y * (R::T / a.mg[MG_LANES] * RY - 4);
+        // rows inside a wave with whole lanes, or any
+        const bool plain = a.mg[MG_VARIANT] == MARCH_PLAIN, two = left >= 2;
+#define RD_BATCH_TILE(M, K, X, RG) march_tile_steps<M, S, RY, W, K, 2, X, RG, false>(a, rows_l, edge_l, tc.x, yb, z0, z1)
+#define RD_BATCH_MODEL(M)                                                                                      \
+    if (two) {                                                                                                 \
+        if (plain) RD_BATCH_TILE(M, 2, false, 0);                                                          \
+        else RD_BATCH_TILE(M, 2, true, 2);                                                                  \
+    } else {                                                                                                   \
+        RD_BATCH_TILE(M, 1, true, 2);                                                                       \
+    }
+        if (en.model == 1) {
+            RD_BATCH_MODEL(Brusselator)
+        } else {
+            RD_BATCH_MODEL(Diffusion<1>)
+        }
+#undef RD_BATCH_MODEL
+#undef RD_BATCH_TILE
+        __syncthreads();                         // the next item refills the exchange
+    }
 }
 
 }  // namespace rdk

@@ -19,7 +19,8 @@ constexpr int kMarchMinLanes = 8;  // lanes of a tile row, at least (the LDS edg
 // StepArgs.mg: lanes of a tile row, halo lanes on each side of it, steps of the
 // plan's launches, and the z chunks of launches of fewer steps (which need not
 // spread their z halo over as many planes)
-enum { MG_LANES = 0, MG_HALO = 1, MG_STEPS = 2, MG_LEFT_CZ = 3, MG_LEFT_CHUNKS = 4 };
+// and in a batch's table the lane exchange (MARCH_*)
+enum { MG_LANES = 0, MG_HALO = 1, MG_STEPS = 2, MG_LEFT_CZ = 3, MG_LEFT_CHUNKS = 4, MG_VARIANT = 5 };
 
 // LDS bytes of shape i for nf fields: two buffers (by plane parity) of the
 // boundary rows of every thread, and of the x-edge cells, at each level.
@@ -75,6 +76,18 @@ hipError_t launch_fmarch_bf16(int cfg, bool cd, bool sr, bool ragged, const Step
 // whole lanes), through LDS, or through LDS with a last lane that is not full.
 // MARCH_MIRROR is added where both x faces are mirrors.
 enum { MARCH_PLAIN = 0, MARCH_EDGES = 1, MARCH_RAGGED = 2, MARCH_MIRROR = 4 };
+
+// Tiles of the batched launch: rows per lane, waves.
+struct BatchMarchCfg { int ry, w; };
+constexpr BatchMarchCfg kBatchMarch = {1, 8};
+
+// One batched launch of up to two steps per grid; workgroups a CU holds.
+hipError_t launch_batched_march(int storage, const int* meta, const BatchEntry* ents, int launch, int blocks, hipStream_t s);
+int batched_march_blocks_per_cu(int storage);
+hipError_t launch_batched_march_f32(const int* meta, const BatchEntry* ents, int launch, int blocks, hipStream_t s);
+hipError_t launch_batched_march_bf16(const int* meta, const BatchEntry* ents, int launch, int blocks, hipStream_t s);
+int batched_march_blocks_per_cu_f32();
+int batched_march_blocks_per_cu_bf16();
 
 // One launch of k steps (1, 2 or the shape's) of shape cfg; `variant` MARCH_*.
 hipError_t launch_march(int storage, int pm, int cfg, int k, int variant, const StepArgs* d, long long blocks,

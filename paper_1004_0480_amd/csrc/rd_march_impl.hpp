@@ -20,13 +20,13 @@ hipError_t run_march_k(int variant, const StepArgs* d, long long blocks, hipStre
     const dim3 grid((unsigned)blocks), block(64 * c.w);
     switch (variant & 3) {
     case MARCH_PLAIN:
-        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, false, false, MIR>), grid, block, 0, s, d);
+        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, false, 0, MIR>), grid, block, 0, s, d);
         break;
     case MARCH_EDGES:
-        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, true, false, MIR>), grid, block, 0, s, d);
+        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, true, 0, MIR>), grid, block, 0, s, d);
         break;
     default:
-        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, true, true, MIR>), grid, block, 0, s, d);
+        hipLaunchKernelGGL((march_kernel<M, S, c.ry, c.w, K, true, 1, MIR>), grid, block, 0, s, d);
         break;
     }
     return hipGetLastError();

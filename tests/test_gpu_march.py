@@ -178,3 +178,38 @@ def test_march_refusals():
     g.set_rounding("nearest")
     assert g.plan()["kernel"] == 8
     g.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_batched_march_bitwise(storage):
+    """Grids of a batch against the same grids alone: even and odd step counts
+    and ticks, rows inside a wave, across waves and ragged, all faces; and a
+    batch with a grid the register march does not take."""
+    import torch
+    cases = [("diffusion", (32, 32, 32), "mirror", 9), ("brusselator", (20, 33, 64), "periodic", 6),
+             ("diffusion", (5, 40, 101), "periodic", 7), ("brusselator", (33, 17, 48), "ghost_lo", 1),
+             ("diffusion", (48, 48, 48), "ghost_hi", 0), ("brusselator", (9, 130, 140), "mirror", 4)]
+    held = ("diffusion", (12, 20, 40), (HELD, MIRROR, MIRROR, MIRROR), 5)
+    for extra in ((), (held,)):
+        for chunk in (1, 3, 4, 20):
+            stream = torch.cuda.Stream()
+            b = rd.Batch(8, 1 << 34, storage, stream=stream)
+            grids, refs = [], []
+            for model, shape, faces, steps in tuple(cases) + extra:
+                spec = spec_of(model, shape, FACES[faces] if isinstance(faces, str) else faces)
+                f = fields_of(shape, spec.ns, steps)
+                refs.append(run(spec, shape, f, storage, [steps], dict(kernel="direct"))[0])
+                g = rd.Grid(shape, spec.ns, spec.h, storage, stream=stream)
+                g.set_model(spec)
+                for s, x in enumerate(f):
+                    g.write(s, x)
+                b.add(g, steps)
+                grids.append(g)
+            done = []
+            while len(done) < len(grids):
+                done += b.step(chunk)
+            for g, ref in zip(grids, refs):
+                assert same(g.read_all(np.float32), ref), (g.shape, chunk, len(extra))
+            b.close()
+            for g in grids:
+                g.close()
