@@ -389,6 +389,8 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
 
 // The one-pass front plan in its register-march form.
 bool is_fmarch(const rd_plan& p) { return p.kernel == RD_KERNEL_FUSED && p.vx == 0; }
+// A register-march plan of any model.
+bool is_march(const rd_plan& p) { return p.kernel == RD_KERNEL_MARCH || is_fmarch(p); }
 
 constexpr int kFrontHalo = 2;   // rows a tile of the front kernel loses on each side
 
@@ -879,9 +881,18 @@ bool one_pass(const rd_grid* g) {
 }
 
 // Resolve the plan in use, fill tiling into the argument copies, upload them.
-int apply_plan(rd_grid* g) {
+// A register-march plan takes fewer integrators, roundings and faces than the
+// plans that autotuning found before it: `named` (rd_set_plan) refuses one that
+// does not fit, but one that was set and ceases to fit by a later setting gives
+// way to the heuristic plan for as long as it does.
+int apply_plan(rd_grid* g, bool named = false) {
     rd_plan p = g->plan;
     int cfg = -1;
+    if (!named && is_march(p) && check_plan(g, p, &cfg) != RD_OK) {
+        const int gc = p.graph_chunk;
+        p = heuristic_plan(g);
+        p.graph_chunk = gc;
+    }
     if (p.kernel == RD_KERNEL_AUTO) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find({g->nx, g->ny, g->nz, g->ns, tune_model_key(g), g->storage});
@@ -1557,7 +1568,7 @@ extern "C" int rd_set_plan(rd_grid* g, const rd_plan* p) {
     RD_HIP(hipStreamSynchronize(g->stream));
     const rd_plan old = g->plan;
     g->plan = *p;
-    const int rc = apply_plan(g);
+    const int rc = apply_plan(g, true);
     if (rc) {
         g->plan = old;
         (void)apply_plan(g);
@@ -1589,17 +1600,6 @@ extern "C" int rd_set_rounding(rd_grid* g, int32_t mode, uint64_t seed) {
     if (mode == RD_ROUND_STOCHASTIC && g->has_model && g->integrator >= RD_RK2)
         return fail(RD_EINVAL, "stochastic rounding takes forward Euler steps");
     RD_HIP(hipStreamSynchronize(g->stream));
-    if (g->has_model && (g->plan.kernel == RD_KERNEL_MARCH || is_fmarch(g->plan))) {
-        // a plan asked for by name has to take the rounding
-        const int old = g->sr_mode;
-        int cfg = -1;
-        g->sr_mode = mode;
-        const int rc = check_plan(g, g->plan, &cfg);
-        if (rc) {
-            g->sr_mode = old;
-            return rc;
-        }
-    }
     g->sr_mode = mode;
     g->sr_seed = uint32_t(seed);
     if (!g->has_model) return RD_OK;
@@ -2011,7 +2011,7 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
     // negative if the plan does not apply, rc set on a device error
     auto time_plan = [&](const rd_plan& p, int steps) -> float {
         g->plan = p;
-        if (apply_plan(g) != RD_OK) return -1.f;
+        if (apply_plan(g, true) != RD_OK) return -1.f;
         float ms = -1.f;
         if ((rc = step_grid(g, 2)) != RD_OK) return -1.f;
         if (hipEventRecord(e0, g->stream) != hipSuccess) { rc = fail(RD_EDEVICE, "event"); return -1.f; }

@@ -164,18 +164,34 @@ def test_march_refusals():
     rk = spec_of("diffusion", (8, 8, 64), mirror)
     rk.integrator = "rk2"
     refused(rk, (8, 8, 64), **p)
-    # a plan asked for by name has to take a rounding that is set later
-    spec = spec_of("brusselator", (8, 8, 64), mirror)
-    g = rd.Grid((8, 8, 64), 2, spec.h, "bf16")
+
+def test_march_plan_gives_way_to_later_settings():
+    """A register-march plan that was set by name (as from autotune) and does
+    not take a rounding, integrator or face set later gives way while it
+    cannot run, and comes back."""
+    shape, mirror = (8, 8, 64), FACES["mirror"]
+    p = dict(kernel="march", vx=4, ry=1, waves=8, prefetch=2)
+    spec = spec_of("brusselator", shape, mirror)
+    rk, held = spec_of("brusselator", shape, mirror), spec_of("brusselator", shape, (HELD,) + mirror[1:])
+    rk.integrator = "rk2"
+    f = fields_of(shape, 2, 8)
+    g = rd.Grid(shape, 2, spec.h, "bf16")
     g.set_model(spec)
     g.set_plan(**p)
-    with pytest.raises(rd.RDError):
-        g.set_rounding("stochastic", 1)
-    g.set_plan()
-    g.set_rounding("stochastic", 1)
-    g.step(3)
-    assert g.plan()["kernel"] != 8
-    g.set_rounding("nearest")
+    assert g.plan()["kernel"] == 8
+    for other, rounding in ((spec, 1), (rk, None), (held, None)):
+        g.set_model(other)
+        if rounding is not None:
+            g.set_rounding("stochastic", rounding)
+        assert g.plan()["kernel"] != 8
+        for s, x in enumerate(f):
+            g.write(s, x)
+        g.step(3)
+        assert same(g.read_all(np.float32), run(other, shape, f, "bf16", [3], dict(kernel="direct"), rounding=rounding)[0])
+        if rounding is not None:
+            g.set_rounding("nearest")
+            assert g.plan()["kernel"] == 8
+    g.set_model(spec)
     assert g.plan()["kernel"] == 8
     g.close()
 
