@@ -195,6 +195,14 @@ int batched_march_blocks_per_cu(int storage) {
     return storage == ST_F32 ? batched_march_blocks_per_cu_f32() : batched_march_blocks_per_cu_bf16();
 }
 
+hipError_t launch_march19(int storage, int pm, int k, bool ragged, const StepArgs* d, long long blocks, hipStream_t s) {
+    switch (storage) {
+    case ST_F32: return launch_march19_f32(pm, k, ragged, d, blocks, s);
+    case ST_BF16: return launch_march19_bf16(pm, k, ragged, d, blocks, s);
+    default: return hipErrorNotSupported;
+    }
+}
+
 hipError_t launch_fmarch(int storage, int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks,
                          hipStream_t s) {
     switch (storage) {
@@ -389,8 +397,31 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
 
 // The one-pass front plan in its register-march form.
 bool is_fmarch(const rd_plan& p) { return p.kernel == RD_KERNEL_FUSED && p.vx == 0; }
+// The LDS plan of 19-point grids in its register-march form.
+bool is_march19(const rd_plan& p) { return p.kernel == RD_KERNEL_LDS && p.vx == 0; }
 // A register-march plan of any model.
-bool is_march(const rd_plan& p) { return p.kernel == RD_KERNEL_MARCH || is_fmarch(p); }
+bool is_march(const rd_plan& p) { return p.kernel == RD_KERNEL_MARCH || is_fmarch(p) || is_march19(p); }
+
+// Lane geometry of a 19-point march tile worth `ry` whole rows (the plan's ry):
+// rows of 16, 32 or 64 lanes, the first that is worth as much, so that none
+// crosses a wave; whole rows where they fit (periodic ones only if they fill
+// the wave the lanes rotate in), else tiles with a halo lane on each side.
+MarchGeom march19_lanes(int nx, bool periodic_x, int k, int l) {
+    const int nx4 = (nx + kMarchVX - 1) / kMarchVX;
+    const bool whole = nx4 <= l && (!periodic_x || nx == 64 * kMarchVX);
+    const int rows = 64 * kMarch19Waves / l;
+    if ((!whole && periodic_x && nx % kMarchVX != 0) || rows <= 2 * k) return MarchGeom{};
+    return whole ? MarchGeom{l, 0, 1, rows - 2 * k, rows - 2}
+                 : MarchGeom{l, 1, (nx4 + l - 3) / (l - 2), rows - 2 * k, rows - 2};
+}
+int march19_ry(const MarchGeom& m) { return std::max(1, m.by / m.tx); }
+MarchGeom march19_geom(int nx, bool periodic_x, int k, int ry) {
+    for (int l : {16, 32, 64}) {
+        const MarchGeom m = march19_lanes(nx, periodic_x, k, l);
+        if (m.l && march19_ry(m) == ry) return m;
+    }
+    return MarchGeom{};
+}
 
 constexpr int kFrontHalo = 2;   // rows a tile of the front kernel loses on each side
 
@@ -472,6 +503,21 @@ double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m,
     return march_cost(k, c.ry, c.w, m, nx, ny, nz, cz);
 }
 
+// The 19-point march.
+double march19_time(int storage, int pm, int k, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz, int cz) {
+    const int nf = march19_fields(pm);
+    MarchCost c{};
+    c.instr = (nf == 1 ? 23.0 : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
+    c.latency = 0.9, c.launch = 1.4, c.fill = 0.5;
+    c.tbs = 5.96, c.halo_xy = 0.65, c.halo_z = 0.66;
+    c.halo = k;
+    c.extra = 3 * k - 1;
+    c.cell_bytes = nf * double(elem_size(storage));
+    c.lds = 2LL * k * nf * 16 * 64 * kMarch19Waves;
+    c.vgprs = nf == 1 ? (k == 1 ? 64 : 96) : k == 1 ? 112 : 188;
+    return march_cost(c, 1, kMarch19Waves, m, nx, ny, nz, cz);
+}
+
 bool march_axes(const StepArgs& a, int nf) {
     // the fields of a pass share their face rules: mirror or periodic along y
     // and z, and mirror, periodic or a fixed ghost value along x
@@ -495,10 +541,11 @@ int march_variant(const StepArgs& a) {
 
 // Decomposition of a tiled plan: fills tiles_* / cz, returns workgroups.
 long long set_tiling(StepArgs& a, const rd_plan& p, int storage = ST_F32, int pm = -1) {
-    const bool front = is_fmarch(p);
-    if (p.kernel == RD_KERNEL_MARCH || front) {
-        const MarchGeom g = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC,
-                                       {p.ry, p.waves, front ? kFrontHalo : p.prefetch});
+    const bool front = is_fmarch(p), s19 = is_march19(p);
+    if (is_march(p)) {
+        const bool per = a.bck[0][0] == BC_PERIODIC;
+        const MarchGeom g = s19 ? march19_geom(a.nx, per, p.prefetch, p.ry)
+                                : march_geom(a.nx, a.ny, per, {p.ry, p.waves, front ? kFrontHalo : p.prefetch});
         a.mg[MG_LANES] = g.l;
         a.mg[MG_HALO] = g.halo;
         a.mg[MG_STEPS] = p.prefetch;
@@ -509,7 +556,8 @@ long long set_tiling(StepArgs& a, const rd_plan& p, int storage = ST_F32, int pm
             double best = 1e300;
             for (int n = 1; n <= 64 && n <= a.nz; ++n) {
                 const int cz = (a.nz + n - 1) / n;
-                const double us = march_time(storage, pm, {p.ry, p.waves, 1}, g1, a.nx, a.ny, a.nz, cz);
+                const double us = s19 ? march19_time(storage, pm, 1, g1, a.nx, a.ny, a.nz, cz)
+                                      : march_time(storage, pm, {p.ry, p.waves, 1}, g1, a.nx, a.ny, a.nz, cz);
                 if (us < best) {
                     best = us;
                     a.mg[MG_LEFT_CZ] = cz;
@@ -690,6 +738,38 @@ bool march_plan(const rd_grid* g, int shape, rd_plan* out) {
     return best < 1e300;
 }
 
+// The same for the 19-point march, with a workgroup for every CU where the
+// grid has as many chunks; `steps` and `lanes` 0: any.
+bool march19_plan(const rd_grid* g, int steps, int lanes, rd_plan* out) {
+    double best = 1e300;
+    const StepArgs& a = g->args[0][0];
+    for (int k = 1; k <= kMarch19MaxSteps; ++k)
+        for (int l : {16, 32, 64}) {
+            const MarchGeom m = march19_lanes(a.nx, a.bck[0][0] == BC_PERIODIC, k, l);
+            if (m.l == 0 || (steps && k != steps) || (lanes && l != lanes)) continue;
+            rd_plan p{};
+            p.kernel = RD_KERNEL_LDS;
+            p.ry = march19_ry(m);
+            p.waves = kMarch19Waves;
+            p.prefetch = k;
+            int cfg = -1;
+            if (check_plan(g, p, &cfg) != RD_OK || march19_geom(a.nx, a.bck[0][0] == BC_PERIODIC, k, p.ry).l != l)
+                continue;
+            const int64_t tiles = int64_t(m.tx) * ((g->ny + m.by - 1) / m.by), most = std::min<int64_t>(g->nz, 64);
+            for (int64_t n = std::min(most, (num_cus() + tiles - 1) / tiles); n <= most; ++n) {
+                p.cz = int((g->nz + n - 1) / n);
+                double us = 0.0;
+                for (int i = 0; i < g->npass; ++i)
+                    us += march19_time(g->storage, g->pass_pm[i], k, m, g->nx, g->ny, g->nz, p.cz);
+                if (us / k < best) {
+                    best = us / k;
+                    *out = p;
+                }
+            }
+        }
+    return best < 1e300;
+}
+
 rd_plan heuristic_plan(const rd_grid* g) {
     rd_plan best{};
     best.kernel = RD_KERNEL_DIRECT;
@@ -720,6 +800,10 @@ rd_plan heuristic_plan(const rd_grid* g) {
         }
     }
     if (g->args[0][0].s19) {
+        // the 19-point march wherever it applies (us per step of Turing FP32
+        // against the ring or direct plan chosen below: 192^3 20.8 and 44.5,
+        // 256^3 42.4 and 67.8 (tuned ring 46.6), 130x101x77 8.5 and 59.6, 32^3 5.2 and 6.8)
+        if (march19_plan(g, 0, 0, &best)) return best;
         // 19-point: the first LDS-ring shape this grid and model take, with
         // z chunks that give about two workgroups per CU; else direct
         for (int i = 0; i < kNumLdsCfgs; ++i) {
@@ -770,6 +854,28 @@ int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
             if (!((block_mask(g->storage, g->pass_pm[k]) >> cfg) & 1u))
                 return fail(RD_EINVAL, "slab shape not compiled for this model and storage");
         *cfg_out = cfg;
+        return RD_OK;
+    }
+    if (is_march19(p)) {
+        if (!g->args[0][0].s19 || p.waves != kMarch19Waves || p.prefetch < 1 || p.prefetch > kMarch19MaxSteps)
+            return fail(RD_EINVAL, "LDS ring shape not available");
+        if (g->integrator >= RD_RK2 || g->sr_mode != RD_ROUND_NEAREST)
+            return fail(RD_EINVAL, "register-march plans take forward Euler and rounding to nearest");
+        if (p.cz < 0) return fail(RD_EINVAL, "cz must be >= 0");
+        if (g->ny < p.prefetch || g->nz < p.prefetch || g->plane * int64_t(elem_size(g->storage)) >= (1LL << 31))
+            return fail(RD_EINVAL, "grid too small or its planes too large for the register march");
+        for (int k = 0; k < g->npass; ++k) {
+            const StepArgs& a = g->args[0][k];
+            const int nf = march19_fields(g->pass_pm[k]);
+            if (nf == 0 || g->storage == RD_F16)
+                return fail(RD_EINVAL, "the 19-point register march is not compiled for this model and storage");
+            if (!march_axes(a, nf))
+                return fail(RD_EINVAL, "the register march takes fields that share mirror or periodic faces "
+                                       "(fixed ghosts along x only)");
+            if (march19_geom(a.nx, a.bck[0][0] == BC_PERIODIC, p.prefetch, p.ry).l == 0)
+                return fail(RD_EINVAL, "the register march has no such tile for this grid");
+        }
+        *cfg_out = 0;
         return RD_OK;
     }
     if (p.kernel == RD_KERNEL_LDS) {
@@ -922,6 +1028,8 @@ int apply_plan(rd_grid* g, bool named = false) {
                     g->variant = march_variant(a);
                     if (a.bck[0][0] == BC_MIRROR && a.bck[0][1] == BC_MIRROR) g->variant |= MARCH_MIRROR;
                 }
+                if (is_march19(p))
+                    g->march_rows = march19_geom(a.nx, a.bck[0][0] == BC_PERIODIC, p.prefetch, p.ry).by + 2 * p.prefetch;
                 (void)set_tiling(g->rk_args[par][k], p);
                 (void)set_tiling(g->rk3_args[par][k], p);
             } else {
@@ -967,6 +1075,9 @@ int apply_plan(rd_grid* g, bool named = false) {
 }
 
 
+// A plan of launch_march_steps.
+bool several_steps(const rd_grid* g) { return g->eff.kernel == RD_KERNEL_MARCH || is_march19(g->eff); }
+
 // One launch of `steps` steps of the register march.
 int launch_march_steps(rd_grid* g, int parity, int steps) {
     for (int k = 0; k < g->npass; ++k) {
@@ -974,15 +1085,18 @@ int launch_march_steps(rd_grid* g, int parity, int steps) {
         const int by = g->march_rows - 2 * steps;
         const int chunks = steps == a.mg[MG_STEPS] ? a.chunks_z : a.mg[MG_LEFT_CHUNKS];
         const long long blocks = (long long)a.tiles_x * ((a.ny + by - 1) / by) * chunks;
-        const hipError_t e = launch_march(g->storage, g->pass_pm[k], g->cfg, steps, g->variant,
-                                          g->d_args + parity * 2 + k, blocks, g->stream);
+        const StepArgs* d = g->d_args + parity * 2 + k;
+        const hipError_t e =
+            is_march19(g->eff)
+                ? launch_march19(g->storage, g->pass_pm[k], steps, a.nx % kMarchVX != 0, d, blocks, g->stream)
+                : launch_march(g->storage, g->pass_pm[k], g->cfg, steps, g->variant, d, blocks, g->stream);
         if (e != hipSuccess) return fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
     }
     return RD_OK;
 }
 
 int launch_one_step(rd_grid* g, int parity) {
-    if (g->eff.kernel == RD_KERNEL_MARCH) return launch_march_steps(g, parity, g->eff.prefetch);
+    if (several_steps(g)) return launch_march_steps(g, parity, g->eff.prefetch);
     if (one_pass(g)) {
         const StepArgs& a = g->args[parity][1];
         const hipError_t e =
@@ -1037,13 +1151,13 @@ int launch_rk_step(rd_grid* g) {
 
 // Time steps one launch of the plan advances.
 int steps_per_launch(const rd_grid* g) {
-    return g->eff.kernel == RD_KERNEL_LDS2 ? 2 : g->eff.kernel == RD_KERNEL_MARCH ? g->eff.prefetch : 1;
+    return g->eff.kernel == RD_KERNEL_LDS2 ? 2 : several_steps(g) ? g->eff.prefetch : 1;
 }
 
 // What is left of a count that is not a multiple of the plan's steps per
 // launch: one launch of the returned number of steps.
 int launch_left(rd_grid* g, int parity, int64_t n, int* rc) {
-    if (g->eff.kernel == RD_KERNEL_MARCH) {
+    if (several_steps(g)) {
         const int steps = n >= 2 && g->eff.prefetch > 2 ? 2 : 1;
         if (steps == 1 && g->left_cfg >= 0) {
             const hipError_t e = launch_pass(g->storage, g->pass_pm[0], RD_KERNEL_BLOCK, g->left_cfg,
@@ -1957,6 +2071,16 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
             cands.push_back(p);
         }
     }
+    for (int k = 1; k <= kMarch19MaxSteps && g->args[0][0].s19; ++k)
+        for (int l : {16, 32, 64}) {
+            rd_plan p{};
+            if (!march19_plan(g, k, l, &p)) continue;
+            const MarchGeom m = march19_lanes(int(g->nx), g->args[0][0].bck[0][0] == BC_PERIODIC, k, l);
+            for (int cz : march_chunks(g, m, p.cz)) {
+                p.cz = cz;
+                cands.push_back(p);
+            }
+        }
     for (int i = 0; i < kNumLds2Cfgs && g->npass == 1; ++i) {
         const LdsCfg c = kLds2Cfgs[i];
         if (g->nx != 256 * c.nch || !lds2_ok(g->storage, g->pass_pm[0], i)) continue;

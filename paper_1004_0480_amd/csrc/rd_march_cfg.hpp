@@ -72,6 +72,16 @@ hipError_t launch_fmarch(int storage, int cfg, bool cd, bool sr, bool ragged, co
 hipError_t launch_fmarch_f32(int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
 hipError_t launch_fmarch_bf16(int cfg, bool cd, bool sr, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
 
+// The 19-point register march (rd_march19.hpp): eight waves a workgroup, one
+// row of four cells per lane, one or two steps a launch.
+constexpr int kMarch19Waves = 8, kMarch19MaxSteps = 2;
+constexpr int march19_fields(int pm) {
+    return pm == PM_DIFF1 ? 1 : pm == PM_BRUSS || pm == PM_TURING ? 2 : 0;
+}
+hipError_t launch_march19(int storage, int pm, int k, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
+hipError_t launch_march19_f32(int pm, int k, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
+hipError_t launch_march19_bf16(int pm, int k, bool ragged, const StepArgs* d, long long blocks, hipStream_t s);
+
 // The lane exchange a geometry needs: none (rows lie inside a wave and end at
 // whole lanes), through LDS, or through LDS with a last lane that is not full.
 // MARCH_MIRROR is added where both x faces are mirrors.

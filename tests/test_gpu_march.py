@@ -24,7 +24,7 @@ SHAPES = [(9, 37, 64), (7, 40, 101), (20, 23, 256), (6, 33, 29), (5, 11, 2060), 
 
 def spec_of(model, shape, faces):
     s = (W.diffusion_spec() if model == "diffusion" else W.brusselator_spec() if model == "brusselator" else
-         W.pollutant_spec(shape, 5, ns=int(model[-1]), nsrc=40))
+         W.turing_spec() if model == "turing" else W.pollutant_spec(shape, 5, ns=int(model[-1]), nsrc=40))
     if model == "diffusion":
         s.K = [[1.0, 0.7, 0.4]]
     xl, xh, y, z = faces
@@ -229,3 +229,40 @@ def test_batched_march_bitwise(storage):
             b.close()
             for g in grids:
                 g.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("model", ["diffusion", "brusselator", "turing"])
+def test_march19_plans_bitwise(model, storage):
+    """The 19-point march (an LDS plan with vx = 0, whose ry is the whole-row
+    worth of a tile): rows of one tile and of several, of every lane count,
+    ragged ends and all faces; left steps; and the default plan, which also has
+    to take the grids that the march refuses."""
+    for shape in SHAPES + [(3, 31, 56), (8, 29, 57), (5, 18, 240), (6, 4, 256)]:
+        for name, faces in dict(FACES, held=(HELD, MIRROR, MIRROR, MIRROR), ghost_y=(MIRROR, MIRROR, GHOST, MIRROR)).items():
+            spec = spec_of(model, shape, faces)
+            spec.stencil = 19
+            spec.K = [[max(k)] * 3 for k in spec.K]
+            f = fields_of(shape, spec.ns, 9)
+            ref, _ = run(spec, shape, f, storage, [5], dict(kernel="direct"))
+            got, used = run(spec, shape, f, storage, [5])
+            assert same(got, ref), (model, shape, name, used)
+            if name in ("held", "ghost_y") or (name == "periodic" and shape[2] % 4):
+                assert (used["kernel"], used["vx"]) != (rd.KERNEL["lds"], 0)
+                continue
+            assert (used["kernel"], used["vx"]) == (rd.KERNEL["lds"], 0)
+            g = rd.Grid(shape, spec.ns, spec.h, storage)
+            g.set_model(spec)
+            plans = []
+            for k in (1, 2):
+                for ry in range(1, 33):
+                    try:
+                        g.set_plan(kernel="lds", vx=0, ry=ry, waves=8, prefetch=k, cz=3)
+                        plans.append(g.plan())
+                    except rd.RDError as e:
+                        assert e.code == rd.EINVAL
+            g.close()
+            assert {p["prefetch"] for p in plans} == {1, 2}
+            for plan in plans:
+                got, _ = run(spec, shape, f, storage, [2, 3], dict(plan, kernel="lds"))
+                assert same(got, ref), (model, shape, name, plan)
