@@ -41,11 +41,16 @@
 // before, against this): diffusion 512^3 FP32 189 -> 77 (K 4: 1740 Gcell/s, 2.2
 // times what the bytes of single steps would allow at 8 TB/s), BF16 121 -> 68;
 // Brusselator 256^3 FP32 44.3 -> 28.0, BF16 42.3 -> 28.2; pollutant 512x512x128
-// FP32 218 -> 170; small grids, where a launch is the latency of its chain of
+// FP32 218 -> 131; small grids, where a launch is the latency of its chain of
 // loads: diffusion 64^3 6.1 -> 2.5, Brusselator 101x90x77 10.2 -> 4.9.  At
 // diffusion 512^3, K 2, the vector units were busy 59 % of the time and 5.3 TB/s
 // moved; non-temporal stores gained 2 % there and cost the Brusselator, whose
 // fields stay in the last cache, 20 %.
+//
+// Point sources: a plane that has any in the tile's rows takes a second copy of
+// the cell code; the others have neither a branch per cell nor its waits (with
+// them, and the wind and the source rows looked up plane by plane, the pollutant
+// took 171 us instead of 131, 256x256x64 37.8 instead of 28.1).
 #pragma once
 
 #include "rd_march_cfg.hpp"
@@ -215,6 +220,11 @@ __device__ __forceinline__ void march_tile_steps(const StepArgs& a, RD_LDS float
         so[r] = stored_x && yl >= KG && yl < KG + BY && y < a.ny ? unsigned(y * a.pitch + x) * ES : 0x80000000u;
         if constexpr (M::SOURCES) yr[r] = ym;
     }
+
+    // rows ys0 .. ys1 - 1 hold every source of the tile (rows beyond a mirror
+    // face reflect into the tile, those beyond a periodic one wrap out of it)
+    const bool all_rows = pery && (yb < KG || yb + BY + KG > a.ny);
+    const int ys0 = all_rows ? 0 : max(yb - KG, 0), ys1 = all_rows ? a.ny : min(yb + BY + KG, a.ny);
 
     // ---- exchange slots ------------------------------------------------------
     // boundary rows: slot t; the rows above and below are those of t -+ L
@@ -394,36 +404,87 @@ __device__ __forceinline__ void march_tile_steps(const StepArgs& a, RD_LDS float
                 if constexpr (RAG != 1) right[f] = in_r ? (XEX ? xr[f] : cr[f]) : right[f];
             }
         }
-        int s0 = 0, s1 = 0;
+        auto cells = [&](auto src) __attribute__((always_inline)) {
+            // emissions of the lane's cells; where there are none -0, which
+            // leaves a sum as it is
+            float e[NF][4];
+            if constexpr (src.value) {
+                const int s0 = cload_ptr<int>(a.src_row)[src_row + yr[r]];
+                const int s1 = cload_ptr<int>(a.src_row)[src_row + yr[r] + 1];
+                bool any[4] = {};
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) e[f][i] = 0.f;
+                for (int q = s0; q < s1; ++q) {
+                    const int d = cload_ptr<int>(a.src_x)[q] - xm, sp = cload_ptr<int>(a.src_sp)[q] - a.sp0;
+                    const float rate = cload_ptr<float>(a.src_rate)[q];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        any[i] = any[i] || d == i;
+#pragma unroll
+                        for (int f = 0; f < NF; ++f) e[f][i] = d == i && sp == f ? rate : e[f][i];
+                    }
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) e[f][i] = any[i] ? e[f][i] : -0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                Nb n[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    n[f].c = c[f][i];
+                    n[f].xm = i > 0 ? c[f][i - 1] : left[f];
+                    n[f].xp = i < 3 ? c[f][i + 1] : right[f];
+                    n[f].ym = r > 0 ? v[f][r > 0 ? r - 1 : 0][i] : h.up[f][i];
+                    n[f].yp = r < RY - 1 ? v[f][r < RY - 1 ? r + 1 : 0][i] : h.dn[f][i];
+                    n[f].zm = vm[f][r][i];
+                    n[f].zp = vp[f][i];
+                }
+                float ei[NF], oi[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) ei[f] = src.value ? e[f][i] : 0.f;
+                M::cell(k, n, wind, src.value, ei, oi);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) o[f][i] = oi[f];
+            }
+        };
+        // (src_row is the same for every lane, so rows of no source take a path
+        // without a branch per cell)
         if constexpr (M::SOURCES) {
             if (src_row >= 0) {
-                s0 = cload_ptr<int>(a.src_row)[src_row + yr[r]];
-                s1 = cload_ptr<int>(a.src_row)[src_row + yr[r] + 1];
+                cells(std::true_type{});
+                return;
             }
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            Nb n[NF];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                n[f].c = c[f][i];
-                n[f].xm = i > 0 ? c[f][i - 1] : left[f];
-                n[f].xp = i < 3 ? c[f][i + 1] : right[f];
-                n[f].ym = r > 0 ? v[f][r > 0 ? r - 1 : 0][i] : h.up[f][i];
-                n[f].yp = r < RY - 1 ? v[f][r < RY - 1 ? r + 1 : 0][i] : h.dn[f][i];
-                n[f].zm = vm[f][r][i];
-                n[f].zp = vp[f][i];
-            }
-            Emission<NF> em{};
+        cells(std::false_type{});
+    };
+
+    // The wind of the next 64 centre planes of level 1, one per lane, and which
+    // of them hold a source in the tile's rows, one per bit: looked up a plane at a time they
+    // would each put a scalar load's latency before that plane's barrier.
+    float wind_t = 0.f;
+    unsigned long long srow_t = 0;
+    auto tables = [&](int p) __attribute__((always_inline)) {
+        if constexpr (M::WIND == WIND_PLANE || M::SOURCES) {
+            const int pz = march_index(min(p + lane, a.nz + K - 2), a.nz, perz);
+            wind_t = plane_wind<M>(a, pz);
             if constexpr (M::SOURCES) {
-                if (src_row >= 0) em = cell_sources<NF>(a, xm + i, s0, s1);
+                const int q = pz * a.ny;
+                srow_t = __ballot(cload_ptr<int>(a.src_row)[q + ys0] < cload_ptr<int>(a.src_row)[q + ys1]);
             }
-            float oi[NF];
-            M::cell(k, n, wind, em.any, em.e, oi);
-#pragma unroll
-            for (int f = 0; f < NF; ++f) o[f][i] = oi[f];
         }
     };
+    float wind[K];
+    int srow[K];
+#pragma unroll
+    for (int l = 0; l < K; ++l) {
+        wind[l] = 0.f;
+        srow[l] = -1;
+    }
 
     auto plane = [&](int p, auto jc) __attribute__((always_inline)) {
         constexpr int J = decltype(jc)::value;
@@ -434,21 +495,17 @@ __device__ __forceinline__ void march_tile_steps(const StepArgs& a, RD_LDS float
         export_plane(par, 0, V[I1]);
 #pragma unroll
         for (int l = 1; l < K; ++l) export_plane(par, l, Q[l - 1][par]);
-        // wind and source ranges of the planes the levels compute
-        float wind[K];
-        int srow[K];
+        // wind and sources of the planes the levels compute: level l's are those
+        // of level l - 1 a plane ago
 #pragma unroll
-        for (int l = 0; l < K; ++l) {
-            // (the first iterations' planes of the upper levels are not needed:
-            // any plane of the tables will do)
-            const int pz = march_index(min(max(p - l, 1 - K), a.nz + K - 2), a.nz, perz);
-            wind[l] = plane_wind<M>(a, pz);
-            srow[l] = -1;
-            if constexpr (M::SOURCES) {
-                const int q = pz * a.ny;
-                if (cload_ptr<int>(a.src_row)[q] < cload_ptr<int>(a.src_row)[q + a.ny]) srow[l] = q;
-            }
+        for (int l = K - 1; l > 0; --l) {
+            wind[l] = wind[l - 1];
+            srow[l] = srow[l - 1];
         }
+        if constexpr (M::WIND == WIND_PLANE)
+            wind[0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wind_t), (p - pa_) & 63));
+        if constexpr (M::SOURCES)
+            srow[0] = (srow_t >> ((p - pa_) & 63)) & 1 ? march_index(min(p, a.nz + K - 2), a.nz, perz) * a.ny : -1;
         lds_done();
         ring_barrier();
         Halo h[K];
@@ -503,6 +560,7 @@ __device__ __forceinline__ void march_tile_steps(const StepArgs& a, RD_LDS float
         });
     };
     for (int p = pa_; p <= pb_; p += 4) {
+        if (((p - pa_) & 63) == 0) tables(p);
         plane(p, std::integral_constant<int, 0>{});
         if (p + 1 > pb_) break;
         plane(p + 1, std::integral_constant<int, 1>{});
