@@ -64,14 +64,60 @@ def kernel_source_digest() -> str:
 
 
 KERNEL_NAMES = {1: "direct_kernel", 2: "tiled_kernel", 3: "block_kernel", 4: "lds_kernel", 5: "lds2_kernel",
-                6: "fch_kernel", 7: "tr_kernel"}
+                6: "fch_kernel", 7: "tr_kernel", 8: "march_kernel"}
+# the register-march forms of two plan kinds: their plans have vx = 0
+MARCH_FORMS = {6: "fmarch_kernel", 4: "march19_kernel"}
 
 
-def measured_traffic(name: str, digest: str, kernel: int = 0):
+def kind_of(traced: str) -> str:
+    """The kind of a traced step kernel."""
+    kinds = list(KERNEL_NAMES.values()) + list(MARCH_FORMS.values())
+    return next((v for v in kinds if "rdk::" + v in traced), "kernel")
+
+
+def kernel_name(plan: dict) -> str:
+    """The step kernel of a plan."""
+    kind = plan.get("kernel", 0)
+    if kind in MARCH_FORMS and plan.get("vx", 1) == 0:
+        return MARCH_FORMS[kind]
+    return KERNEL_NAMES.get(kind, "?")
+
+
+def plan_steps(plan: dict) -> int:
+    """Time steps one launch of a plan advances."""
+    if plan.get("kernel") == 5:
+        return 2
+    if plan.get("kernel") == 8 or (plan.get("kernel") == 4 and plan.get("vx", 1) == 0):
+        return plan["prefetch"]
+    return 1
+
+
+def trace_steps(name: str) -> int:
+    """The same from a traced kernel's name (the its template arguments hold the
+    march kernels' count)."""
+    if "rdk::lds2_kernel" in name:
+        return 2
+    for kind, at in (("rdk::march_kernel<", 4), ("rdk::march19_kernel<", 3)):
+        if kind in name:
+            depth, args = 0, [""]
+            for ch in name[name.index(kind) + len(kind):]:
+                if ch == ">" and depth == 0:
+                    break
+                depth += (ch == "<") - (ch == ">")
+                if ch == "," and depth == 0:
+                    args.append("")
+                else:
+                    args[-1] += ch
+            return int(args[at])
+    return 1
+
+
+def measured_traffic(name: str, digest: str, kernel=0):
     """The committed rocprofv3 PMC summary of this workload on the kind of
-    kernel the plan runs, if it was taken on the current kernel sources;
-    else None."""
-    path = os.path.join(PROFILES, "%s_%s_pmc.json" % (name, KERNEL_NAMES.get(kernel, "?")))
+    kernel the plan runs (its number or name), if it was taken on the current
+    kernel sources; else None."""
+    kind = kernel if isinstance(kernel, str) else KERNEL_NAMES.get(kernel, "?")
+    path = os.path.join(PROFILES, "%s_%s_pmc.json" % (name, kind))
     try:
         with open(path) as fh:
             rec = json.load(fh)
@@ -81,7 +127,7 @@ def measured_traffic(name: str, digest: str, kernel: int = 0):
         return None
     names = rec.get("kernel")
     names = names if isinstance(names, list) else [names]
-    if kernel and not all(KERNEL_NAMES.get(kernel, "?") in str(n) for n in names):
+    if kernel and not all(kind in str(n) for n in names):
         return None
     return rec
 
@@ -156,7 +202,8 @@ def copy_ceiling(torch, stream, nbytes: int, reps: int = 10):
 # ------------------------------------------------ profile summaries (rocprofv3)
 
 STEP_KERNELS = ("rdk::block_kernel", "rdk::tiled_kernel", "rdk::direct_kernel", "rdk::lds_kernel",
-                "rdk::lds2_kernel", "rdk::fch_kernel", "rdk::tr_kernel")
+                "rdk::lds2_kernel", "rdk::fch_kernel", "rdk::tr_kernel", "rdk::march_kernel", "rdk::march19_kernel",
+                "rdk::fmarch_kernel")
 
 
 def _counter_rows(d: str):
@@ -218,10 +265,10 @@ def pmc_summary(args):
         rd_b += f_k * 1024.0 * rs
         wr_b += w_k * 1024.0 * ws
     cells = int(np.prod(W.DEFAULT_SHAPES[args.workload]))
-    # one launch set reads and writes every field once: one step, or two for
-    # the two-step (temporally blocked) kernel
-    spl = 2 if any("rdk::lds2_kernel" in k for k in knames) else 1
-    one_pass = any("rdk::fch_kernel" in k for k in knames)
+    # one launch set reads and writes every field once, for as many steps as
+    # the kernel blocks in time
+    spl = max(trace_steps(k) for k in knames)
+    one_pass = any("rdk::fch_kernel" in k or "rdk::fmarch_kernel" in k for k in knames)
     bpc = alg_bytes_per_cell(args.workload, args.storage, one_pass)
     alg = bpc * cells
     rec = {"kernel": knames[0] if len(knames) == 1 else knames,
@@ -236,7 +283,7 @@ def pmc_summary(args):
            "hbm_bytes_per_step": (rd_b + wr_b) / spl,
            "alg_bytes_per_cell": bpc, "algorithmic_bytes_per_launch_set": alg,
            "traffic_over_algorithmic": (rd_b + wr_b) / alg}
-    kind = next((v for v in KERNEL_NAMES.values() if v in knames[0]), "kernel")
+    kind = kind_of(knames[0])
     out = os.path.join(PROFILES, "%s_%s_pmc.json" % (profile_name(args), kind))
     with open(out, "w") as fh:
         json.dump(rec, fh, indent=1)
@@ -265,7 +312,7 @@ def counter_summary(args):
                 continue
             lines.append("| %s | %.6g | %s | %d |" % (c, v, "%.4g" % (v / waves) if waves else "-", n))
         lines.append("")
-    kind = next((v for v in KERNEL_NAMES.values() if v in knames[0]), "kernel")
+    kind = kind_of(knames[0])
     out = os.path.join(PROFILES, "%s_%s_counters.md" % (profile_name(args), kind))
     with open(out, "w") as fh:
         fh.write("\n".join(lines) + "\n")
@@ -315,7 +362,7 @@ def trace_summary(args):
                   % (what, bpc, cells, bpc * cells / 1e6),
                   "average %.2f us per step that is %.0f GB/s, %.1f%% of the 8 TB/s HBM peak."
                   % (step[1], gbs, 100.0 * gbs / HBM_PEAK_GBS)]
-    kind = next((v for v in KERNEL_NAMES.values() if step and v in step[0]), "kernel")
+    kind = kind_of(step[0]) if step else "kernel"
     out = os.path.join(PROFILES, "%s_%s_trace.md" % (profile_name(args), kind))
     with open(out, "w") as fh:
         fh.write("\n".join(lines) + "\n")
@@ -467,7 +514,7 @@ def main():
 
     passes = g.passes()
     bpc = alg_bytes_per_cell(args.workload, args.storage, one_pass=passes == 1)
-    steps_per_launch = 2 if plan.get("kernel") == 5 else 1     # two-step (temporally blocked) plan
+    steps_per_launch = plan_steps(plan)     # more than one: temporally blocked
     # a Runge-Kutta step runs 2 or 3 Euler stages; every stage after the first
     # also reads the current state once per species (its combination is
     # fused into the store)
@@ -483,7 +530,7 @@ def main():
     if stages > 1:      # reported per step over all its kernels
         achieved = (stages * bpc + rk_bytes) * w.cells / (ms_per_step * 1e-3) / 1e9
     digest = kernel_source_digest()
-    pmc = measured_traffic(profile_name(args), digest, plan.get("kernel", 0))
+    pmc = measured_traffic(profile_name(args), digest, kernel_name(plan))
     traffic = None
     if pmc is not None and stages == 1 and pmc.get("steps_per_launch", 1) == steps_per_launch:
         traffic = pmc.get("hbm_bytes_per_launch") if passes == 1 else pmc.get("hbm_bytes_per_step")

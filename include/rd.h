@@ -164,11 +164,15 @@ enum { RD_EULER = 1, RD_RK2 = 2, RD_RK3 = 3 };
 /* kernel plan of a grid (all plans give bitwise-identical fields) */
 enum {
     RD_KERNEL_AUTO = 0,    /* library choice: the rd_autotune cache entry for
-                              this shape, model and integrator, else a heuristic
-                              (the one-pass plan for the 7-point front model; a
-                              slab shape for other 7-point models; for 19-point
-                              ones the first LDS-ring shape, with z chunks for
-                              about two workgroups per CU)                      */
+                              this shape, model and integrator, else a heuristic:
+                              a register march where one takes the grid (MARCH,
+                              FUSED or LDS with vx 0), else the one-pass plan for
+                              the 7-point front model, a slab shape for other
+                              7-point models, and for 19-point ones the first
+                              LDS-ring shape, with z chunks for about two
+                              workgroups per CU.  A register-march plan that was
+                              set by name gives way to the heuristic while the
+                              model or rounding is one it does not take         */
     RD_KERNEL_DIRECT = 1,  /* one thread per cell, neighbours through the cache */
     RD_KERNEL_TILED = 2,   /* xy tile per workgroup, z-march register window,
                               wave64 lane shifts for x, LDS for inter-wave rows */
@@ -205,7 +209,11 @@ enum {
 typedef struct rd_plan {
     int32_t kernel;       /* RD_KERNEL_*                                        */
     int32_t vx;           /* TILED/BLOCK: cells per lane along x (1, 2 or 4);
-                             LDS: 4 (rows of <= 256 cells) or 8 (257..512);
+                             LDS: 4 (rows of <= 256 cells) or 8 (257..512), or 0:
+                             the register march of 19-point diffusion (one
+                             species), Brusselator and Turing (FP32 or BF16, under
+                             the conditions of MARCH, any nx; a periodic x axis
+                             needs a multiple of 4);
                              LDS2: 4 (rows of 256 cells) or 8 (of 512);
                              FUSED: waves computing the chemical potential,
                              or 0: the register-march form, every wave computing
@@ -216,7 +224,8 @@ typedef struct rd_plan {
                              TRING: 2 (cells per lane)                         */
     int32_t ry;           /* TILED/BLOCK: rows per wave (1, 2 or 4);
                              LDS/LDS2/FUSED/TRING: rows per workgroup;
-                             MARCH, FUSED with vx 0: rows per lane (1 or 2)    */
+                             MARCH, FUSED with vx 0: rows per lane (1 or 2);
+                             LDS with vx 0: a tile's worth of whole rows        */
     int32_t waves;        /* TILED/BLOCK: waves per workgroup (1 or 4);
                              LDS/LDS2: computing waves (plus one loading wave);
                              FUSED: waves updating the fields (plus vx waves
@@ -224,13 +233,15 @@ typedef struct rd_plan {
                              TRING: computing waves (plus one loading wave, or
                              two when the fields' ring rows times prefetch-3
                              exceed 63 loads);
-                             MARCH, FUSED with vx 0: waves per workgroup       */
+                             MARCH, FUSED and LDS with vx 0: waves per workgroup
+                             (LDS: 8)                                          */
     int32_t cz;           /* TILED/LDS/LDS2/FUSED/TRING/MARCH: z planes per workgroup, 0 = all;
                              BLOCK: planes per slab (2, 4 or 8)                */
     int32_t prefetch;     /* TILED: planes in flight ahead of the z window (1-2);
                              LDS/LDS2/FUSED/TRING: input ring slots;
                              MARCH: time steps per launch (2 to 4; the rest of a
-                             count in launches of two and one); FUSED with vx 0: 1 */
+                             count in launches of two and one); FUSED with vx 0: 1;
+                             LDS with vx 0: time steps per launch (1 or 2)     */
     int32_t order;        /* BLOCK/LDS/LDS2/FUSED/TRING/MARCH: tile enumeration, 0 = x, then y, then z chunk;
                              1 = z chunk fastest (z-neighbour slabs run together
                              on one XCD and share its L2)                       */
@@ -363,7 +374,8 @@ int rd_autotune(rd_grid *g, int32_t trial_steps, rd_plan *best);
 
 /* A batch steps many grids of uneven size together: each launch is one
  * persistent kernel that walks a work list of (grid, tile) items covering
- * every active grid, and rd_batch_step replays a captured hipGraph of such
+ * every active grid (two steps of each where every grid is one that
+ * RD_KERNEL_MARCH takes), and rd_batch_step replays a captured hipGraph of such
  * launches.  Grids must use the DIFFUSION or BRUSSELATOR model, share the
  * batch's storage dtype and stay alive while in the batch.
  * hbm_budget_bytes caps the summed rd_grid_bytes of member grids. */

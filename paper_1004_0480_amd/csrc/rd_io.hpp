@@ -13,7 +13,10 @@ namespace rdk {
 // turn, several at a time (DEPTH) so that several loads of a thread are in
 // flight, or one where a thread has no more than one anyway:
 // one 32-bit division per unit finds its row, where a division in 64 bits per
-// cell would cost more than the cell's bytes.
+// cell would cost more than the cell's bytes.  Bound by memory: 403x301x300 FP32
+// (146 MB a field, traced averages, cell by cell before against this) write
+// 89 -> 68 us, read 84 -> 60, reduction 105 -> 46 (44 us is the write or read at
+// the rate of a streaming copy, 22 the reduction's).
 constexpr int IO_DEPTH = 4;
 constexpr int IO_CELLS = 256 * 4;                 // cells of a workgroup's turn at depth 1
 
