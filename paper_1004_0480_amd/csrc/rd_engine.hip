@@ -381,7 +381,8 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
     const int nx4 = (nx + kMarchVX - 1) / kMarchVX, t = 64 * c.w;
     long long best_n = 0;
     for (int tx = 1; tx <= nx4 && tx <= 4096; ++tx) {
-        const int halo = tx > 1 ? 1 : 0, l = (nx4 + tx - 1) / tx + 2 * halo;
+        // (rows of fewer lanes leave the rest of a tile's least idle)
+        const int halo = tx > 1 ? 1 : 0, l = tx > 1 ? (nx4 + tx - 1) / tx + 2 : std::max(nx4, kMarchMinLanes);
         if (l > t) continue;
         if (l < kMarchMinLanes || (halo && periodic_x && nx % kMarchVX != 0)) break;
         const int rows = t / l * c.ry, by = rows - 2 * c.k;
