@@ -64,23 +64,20 @@ def kernel_source_digest() -> str:
 
 
 KERNEL_NAMES = {1: "direct_kernel", 2: "tiled_kernel", 3: "block_kernel", 4: "lds_kernel", 5: "lds2_kernel",
-                6: "fch_kernel", 7: "tr_kernel", 8: "march_kernel"}
-# the register-march forms of two plan kinds: their plans have vx = 0
-MARCH_FORMS = {6: "fmarch_kernel", 4: "march19_kernel"}
+                6: "fch_kernel", 7: "tr_kernel", 8: "march_kernel",
+                # the register-march forms of two kinds: their plans have vx = 0
+                (6, 0): "fmarch_kernel", (4, 0): "march19_kernel"}
 
 
 def kind_of(traced: str) -> str:
     """The kind of a traced step kernel."""
-    kinds = list(KERNEL_NAMES.values()) + list(MARCH_FORMS.values())
-    return next((v for v in kinds if "rdk::" + v in traced), "kernel")
+    return next((v for v in KERNEL_NAMES.values() if "rdk::" + v in traced), "kernel")
 
 
 def kernel_name(plan: dict) -> str:
     """The step kernel of a plan."""
     kind = plan.get("kernel", 0)
-    if kind in MARCH_FORMS and plan.get("vx", 1) == 0:
-        return MARCH_FORMS[kind]
-    return KERNEL_NAMES.get(kind, "?")
+    return KERNEL_NAMES.get((kind, plan.get("vx", 1)), KERNEL_NAMES.get(kind, "?"))
 
 
 def plan_steps(plan: dict) -> int:
@@ -332,7 +329,7 @@ def trace_summary(args):
     with open(files[0]) as fh:
         rows = list(csv.DictReader(fh))
     cells = int(np.prod(W.DEFAULT_SHAPES[args.workload]))
-    one_pass = any("rdk::fch_kernel" in r["Name"] for r in rows)
+    one_pass = any("rdk::fch_kernel" in r["Name"] or "rdk::fmarch_kernel" in r["Name"] for r in rows)
     bpc = alg_bytes_per_cell(args.workload, args.storage, one_pass)
     lines = ["# rocprofv3 kernel trace: %s step kernel (MI355X)" % profile_name(args), "",
              "Workload: %s, grid (z, y, x) = %s, %s storage, %d-point Laplacian."
@@ -356,12 +353,14 @@ def trace_summary(args):
     step = (passes[0][0], sum(t for _, t in passes)) if passes else None
     if step:
         gbs = bpc * cells / (step[1] * 1e-6) / 1e9
+        spl = trace_steps(step[0])
+        per = "step" if spl == 1 else "launch of %d steps" % spl
         what = "Step kernel `%s`" % step[0][:80] if len(passes) == 1 else \
             "The step's %d passes (`%s` ...)" % (len(passes), step[0][:60])
-        lines += ["%s: %d B/cell algorithmic x %d cells = %.1f MB per step; at the traced"
-                  % (what, bpc, cells, bpc * cells / 1e6),
-                  "average %.2f us per step that is %.0f GB/s, %.1f%% of the 8 TB/s HBM peak."
-                  % (step[1], gbs, 100.0 * gbs / HBM_PEAK_GBS)]
+        lines += ["%s: %d B/cell algorithmic x %d cells = %.1f MB per %s; at the traced"
+                  % (what, bpc, cells, bpc * cells / 1e6, per),
+                  "average %.2f us per %s that is %.0f GB/s, %.1f%% of the 8 TB/s HBM peak."
+                  % (step[1], per, gbs, 100.0 * gbs / HBM_PEAK_GBS)]
     kind = kind_of(step[0]) if step else "kernel"
     out = os.path.join(PROFILES, "%s_%s_trace.md" % (profile_name(args), kind))
     with open(out, "w") as fh:
