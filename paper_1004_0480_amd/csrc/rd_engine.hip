@@ -1687,9 +1687,10 @@ extern "C" int rd_set_plan(rd_grid* g, const rd_plan* p) {
     g->plan = *p;
     const int rc = apply_plan(g, true);
     if (rc) {
+        const std::string why = g_err;     // (choosing the old plan again tries others)
         g->plan = old;
         (void)apply_plan(g);
-        return rc;
+        return fail(rc, why);
     }
     return RD_OK;
 }
