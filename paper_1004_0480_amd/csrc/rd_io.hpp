@@ -14,9 +14,9 @@ namespace rdk {
 // flight, or one where a thread has no more than one anyway:
 // one 32-bit division per unit finds its row, where a division in 64 bits per
 // cell would cost more than the cell's bytes.  Bound by memory: 403x301x300 FP32
-// (146 MB a field, traced averages, cell by cell before against this) write
-// 89 -> 68 us, read 84 -> 60, reduction 105 -> 46 (44 us is the write or read at
-// the rate of a streaming copy, 22 the reduction's).
+// (146 MB a field, fastest traced, cell by cell before against this) write
+// 89 -> 57 us, read 84 -> 53, reduction 105 -> 30, where the bytes at the rate of
+// a streaming copy take 44, 44 and 22.
 constexpr int IO_DEPTH = 4;
 constexpr int IO_CELLS = 256 * 4;                 // cells of a workgroup's turn at depth 1
 
@@ -28,26 +28,40 @@ __device__ __forceinline__ IoUnit io_unit(unsigned u, unsigned units, int nx4, i
     return IoUnit{row0 + r, x, u < units ? min(4, nx - x) : 0};
 }
 
-// Up to four cells of type T; cells past n are 0.  The address need only be
-// aligned to a cell (dense rows start anywhere).
+// The four cells from `at` on of `end` readable ones, moved back where they
+// would pass the end (io_cells puts that right), so that the loads of a turn
+// are one straight run (a branch around each, for the units at the ends of rows:
+// reduction 43 us, read 57).  The address need only be aligned to a cell
+// (dense rows start anywhere).
 template <class T>
-__device__ __forceinline__ Vec<T, 4> io_load(const void* base, long long at, int n) {
-    const RD_GLOBAL T* p = gload_ptr<T>(base) + at;
+__device__ __forceinline__ Vec<T, 4> io_load(const void* base, long long at, long long end) {
     Vec<T, 4> v{};
-    if (n == 4) {
-        __builtin_memcpy(&v, p, 4 * sizeof(T));
-    } else {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (i < n) v.v[i] = p[i];
-    }
+    if (end >= 4) __builtin_memcpy(&v, gload_ptr<T>(base) + min(at, end - 4), 4 * sizeof(T));
     return v;
 }
+// A unit's cells, those past n 0; at the end of the field they are loaded one
+// by one.
+template <class T>
+__device__ __forceinline__ void io_cells(const void* base, long long at, long long end, int n, Vec<T, 4>& v) {
+    if (at + 4 > end && n > 0) {
+        const RD_GLOBAL T* p = gload_ptr<T>(base) + at;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < n) v.v[i] = p[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v.v[i] = i < n ? v.v[i] : T(0);
+}
+// (non-temporal: what is written here passes through once; read 57 -> 53 us,
+// and a reduction after a write 42 -> 36)
 template <class T>
 __device__ __forceinline__ void io_store(void* base, long long at, int n, const Vec<T, 4>& v) {
     RD_GLOBAL T* p = gstore_ptr<T>(base) + at;
     if (n == 4) {
-        __builtin_memcpy(p, &v, 4 * sizeof(T));
+        typedef T vt __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+        vt w;
+        __builtin_memcpy(&w, &v, sizeof(w));
+        __builtin_nontemporal_store(w, (RD_GLOBAL vt*)p);
     } else {
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -83,22 +97,26 @@ __global__ __launch_bounds__(256) void reduce_partial(const void* f, int nx, lon
     const long long row0 = rows * blockIdx.x / gridDim.x, row1 = rows * (blockIdx.x + 1) / gridDim.x;
     const int nx4 = (nx + 3) / 4;
     const unsigned units = unsigned(row1 - row0) * unsigned(nx4);
+    const long long end = (rows - 1) * pitch + (pitch & 3 ? nx : pitch);   // (padded rows are whole units)
     double s[4] = {}, q[4] = {};
     for (unsigned u = threadIdx.x; u < units; u += 256 * IO_DEPTH) {
         Vec<typename S::T, 4> v[IO_DEPTH];
+        IoUnit t[IO_DEPTH];
 #pragma unroll
         for (int k = 0; k < IO_DEPTH; ++k) {
-            const IoUnit t = io_unit(u + 256 * k, units, nx4, nx, row0);
-            v[k] = io_load<typename S::T>(f, t.row * pitch + t.x, t.n);
+            t[k] = io_unit(u + 256 * k, units, nx4, nx, row0);
+            v[k] = io_load<typename S::T>(f, t[k].row * pitch + t[k].x, end);
         }
 #pragma unroll
-        for (int k = 0; k < IO_DEPTH; ++k)
+        for (int k = 0; k < IO_DEPTH; ++k) {
+            io_cells(f, t[k].row * pitch + t[k].x, end, t[k].n, v[k]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const double c = S::up(v[k].v[i]);
                 s[i] += c;
                 q[i] = __fma_rn(c, c, q[i]);
             }
+        }
     }
     double ts = (s[0] + s[1]) + (s[2] + s[3]), tq = (q[0] + q[1]) + (q[2] + q[3]);
     block_sum2(ts, tq);
@@ -136,20 +154,23 @@ __device__ __forceinline__ void convert_rows(const void* src, void* dst, int nx,
     const long long row0 = (long long)blockIdx.x * run;
     const int nx4 = (nx + 3) / 4;
     const unsigned units = unsigned(min((long long)run, rows - row0)) * unsigned(nx4);
+    const long long end = (rows - 1) * in + (in & 3 ? nx : in);
     for (unsigned u = threadIdx.x; u < units; u += 256 * DEPTH) {
         Vec<In, 4> v[DEPTH];
         IoUnit t[DEPTH];
 #pragma unroll
         for (int k = 0; k < DEPTH; ++k) {
             t[k] = io_unit(u + 256 * k, units, nx4, nx, row0);
-            v[k] = io_load<In>(src, t[k].row * in + t[k].x, t[k].n);
+            v[k] = io_load<In>(src, t[k].row * in + t[k].x, end);
         }
 #pragma unroll
         for (int k = 0; k < DEPTH; ++k) {
             Vec<Out, 4> w;
+            io_cells(src, t[k].row * in + t[k].x, end, t[k].n, v[k]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) w.v[i] = down(up(v[k].v[i]));
-            io_store<Out>(dst, t[k].row * out + t[k].x, t[k].n, w);
+            // (padded rows take whole units: zeros past the row's end)
+            io_store<Out>(dst, t[k].row * out + t[k].x, t[k].n > 0 && !(out & 3) ? 4 : t[k].n, w);
         }
     }
 }
