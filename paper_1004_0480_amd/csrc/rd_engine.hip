@@ -90,18 +90,6 @@ PassGroups pass_groups(int model, int ns) {
     return p;
 }
 
-// Workgroups of the layout conversions: runs of whole rows, 4096 cells each
-// (four units of four cells per thread), fewer where that would not give each
-// CU several workgroups.
-struct RowRuns { long long rows; int run; unsigned blocks; bool deep; };
-RowRuns row_runs(int64_t nx, int64_t rows) {
-    const int64_t cells = std::min<int64_t>(IO_DEPTH * IO_CELLS, std::max<int64_t>(IO_CELLS, nx * rows / 2048));
-    // (longer runs where the count of workgroups would not fit a launch)
-    const int64_t row = (nx + 3) / 4 * 4;
-    const int64_t run = std::max<int64_t>({1, cells / row, (rows + 0x3fffffff) / 0x40000000});
-    return RowRuns{(long long)rows, int(run), unsigned((rows + run - 1) / run), run * row > IO_CELLS};
-}
-
 void launch_reduce_partial(int storage, const void* f, int nx, long long rows, int pitch, double* part, int blocks,
                            hipStream_t s) {
     const dim3 grid(blocks), block(256);
@@ -1757,7 +1745,7 @@ extern "C" int rd_write_field(rd_grid* g, int32_t species, const void* src, int3
     const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
 #define RD_PACK_D(S, SRC, D)                                                                               \
     hipLaunchKernelGGL((pack_kernel<S, SRC, D>), dim3(rr.blocks), dim3(256), 0, g->stream, dsrc, dst, int(g->nx), \
-                       rr.rows, rr.run, g->pitch)
+                       rr.rows, rr.run, rr.parts, g->pitch)
 #define RD_PACK(S, SRC)                            \
     if (rr.deep) RD_PACK_D(S, SRC, IO_DEPTH);      \
     else RD_PACK_D(S, SRC, 1)
@@ -1807,7 +1795,7 @@ extern "C" int rd_read_field(rd_grid* g, int32_t species, void* dst, int32_t dst
     const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
 #define RD_UNPACK_D(S, T, D)                                                                                 \
     hipLaunchKernelGGL((unpack_kernel<S, T, D>), dim3(rr.blocks), dim3(256), 0, g->stream, src, static_cast<T*>(ddst), \
-                       int(g->nx), rr.rows, rr.run, g->pitch)
+                       int(g->nx), rr.rows, rr.run, rr.parts, g->pitch)
 #define RD_UNPACK(S)                                        \
     if (dst_dtype == RD_F64) {                              \
         if (rr.deep) RD_UNPACK_D(S, double, IO_DEPTH);      \
@@ -1875,7 +1863,7 @@ extern "C" int rd_chemical_potential(rd_grid* g, float* dst_host) {
     RD_HIP(hipMalloc(&stage, n * sizeof(float)));
     const RowRuns rr = row_runs(g->nx, g->ny * g->nz);
     hipLaunchKernelGGL((unpack_kernel<StF32, float, IO_DEPTH>), dim3(rr.blocks), dim3(256), 0, g->stream, g->aux, stage,
-                       int(g->nx), rr.rows, rr.run, g->pitch);
+                       int(g->nx), rr.rows, rr.run, rr.parts, g->pitch);
     hipError_t e2 = hipGetLastError();
     if (e2 == hipSuccess) e2 = hipStreamSynchronize(g->stream);
     if (e2 == hipSuccess) e2 = hipMemcpy(dst_host, stage, n * sizeof(float), hipMemcpyDeviceToHost);

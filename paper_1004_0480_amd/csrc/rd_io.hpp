@@ -4,22 +4,20 @@
 #pragma once
 
 #include "rd_device.hpp"
+#include "rd_io_cfg.hpp"
 
 namespace rdk {
 
 // Fields are walked as rows (padded rows start every `pitch` cells, dense ones
 // every nx) of units of four cells, the last of a row holding what is left.
-// A workgroup owns a run of whole rows and its threads take the run's units in
-// turn, several at a time (DEPTH) so that several loads of a thread are in
+// A workgroup owns a run of whole rows (or a part of a long one) and its threads
+// take the run's units in turn, several at a time (DEPTH) so that several loads of a thread are in
 // flight, or one where a thread has no more than one anyway:
 // one 32-bit division per unit finds its row, where a division in 64 bits per
 // cell would cost more than the cell's bytes.  Bound by memory: 403x301x300 FP32
 // (146 MB a field, fastest traced, cell by cell before against this) write
 // 89 -> 57 us, read 84 -> 53, reduction 105 -> 30, where the bytes at the rate of
 // a streaming copy take 44, 44 and 22.
-constexpr int IO_DEPTH = 4;
-constexpr int IO_CELLS = 256 * 4;                 // cells of a workgroup's turn at depth 1
-
 struct IoUnit { long long row; int x, n; };       // n cells (0: none) from cell x of a row
 
 __device__ __forceinline__ IoUnit io_unit(unsigned u, unsigned units, int nx4, int nx, long long row0) {
@@ -146,16 +144,20 @@ __global__ __launch_bounds__(256) void reduce_final(const double* part, int n, d
 
 // ------------------------------------------------------ layout conversion
 
-// A workgroup converts `run` rows of `in` cells apart to rows `out` cells
-// apart, cell by cell through `up` and `down` (FP32 between).
+// A workgroup converts `run` rows of `in` cells apart, or one of the `parts` of
+// a row, to rows `out` cells apart, cell by cell through `up` and `down` (FP32
+// between).
 template <int DEPTH, class In, class Out, class Up, class Down>
-__device__ __forceinline__ void convert_rows(const void* src, void* dst, int nx, long long rows, int run, int in,
-                                             int out, Up up, Down down) {
-    const long long row0 = (long long)blockIdx.x * run;
+__device__ __forceinline__ void convert_rows(const void* src, void* dst, int nx, long long rows, int run, int parts,
+                                             int in, int out, Up up, Down down) {
+    const unsigned group = blockIdx.x / unsigned(parts), part = blockIdx.x - group * unsigned(parts);
+    const long long row0 = (long long)group * run;
     const int nx4 = (nx + 3) / 4;
-    const unsigned units = unsigned(min((long long)run, rows - row0)) * unsigned(nx4);
+    const unsigned all = unsigned(min((long long)run, rows - row0)) * unsigned(nx4);
+    const unsigned each = (all + unsigned(parts) - 1) / unsigned(parts);
+    const unsigned first = part * each, units = min(first + each, all);
     const long long end = (rows - 1) * in + (in & 3 ? nx : in);
-    for (unsigned u = threadIdx.x; u < units; u += 256 * DEPTH) {
+    for (unsigned u = first + threadIdx.x; u < units; u += 256 * DEPTH) {
         Vec<In, 4> v[DEPTH];
         IoUnit t[DEPTH];
 #pragma unroll
@@ -178,17 +180,17 @@ __device__ __forceinline__ void convert_rows(const void* src, void* dst, int nx,
 // dense [nz][ny][nx] of transfer type Src -> padded storage S
 template <class S, class Src, int DEPTH>
 __global__ __launch_bounds__(256) void pack_kernel(const void* src, void* dst, int nx, long long rows, int run,
-                                                   int pitch) {
+                                                   int parts, int pitch) {
     convert_rows<DEPTH, typename Src::T, typename S::T>(
-        src, dst, nx, rows, run, nx, pitch, [](typename Src::T v) { return Src::up(v); },
+        src, dst, nx, rows, run, parts, nx, pitch, [](typename Src::T v) { return Src::up(v); },
         [](float v) { return S::down(v); });
 }
 
 template <class S, typename DstT, int DEPTH>
 __global__ __launch_bounds__(256) void unpack_kernel(const void* src, DstT* dst, int nx, long long rows, int run,
-                                                     int pitch) {
+                                                     int parts, int pitch) {
     convert_rows<DEPTH, typename S::T, DstT>(
-        src, dst, nx, rows, run, pitch, nx, [](typename S::T v) { return S::up(v); },
+        src, dst, nx, rows, run, parts, pitch, nx, [](typename S::T v) { return S::up(v); },
         [](float v) { return DstT(v); });
 }
 

@@ -47,3 +47,20 @@ def test_transfers_and_reductions_at_unit_edges(storage):
                         tol = 2.0 * (n + 4) * 2.0 ** -53 * np.abs(terms).sum() * 0.125
                         assert abs(s - terms.sum() * 0.125) <= tol, (shape, shift, src)
         g.close()
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_rows_longer_than_a_workgroup_takes(storage):
+    """Long rows are split between workgroups: rows that end inside a part's
+    last unit, one row and several, every value exact."""
+    import torch
+    for shape in ((1, 1, 70001), (1, 3, 5003), (2, 2, 16384), (1, 1, 1 << 20)):
+        x = (torch.arange(int(np.prod(shape))) % 251).float().cuda().view(shape)    # exact in BF16
+        g = rd.Grid(shape, 1, 1.0, storage)
+        g.set_model(W.ModelSpec("diffusion", 1, 0.01, 1.0, [[1.0] * 3], W.uniform_bc(1, "mirror")))
+        g.write(0, x)
+        out = torch.full(shape, -1.0, device="cuda")
+        g.read_device(0, out)
+        assert torch.equal(out, x), shape
+        assert np.array_equal(g.read(0), x.double().cpu().numpy())
+        g.close()

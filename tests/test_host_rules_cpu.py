@@ -1,0 +1,63 @@
+"""Rules of the engine that are host arithmetic alone, compiled from the
+headers the library is built from."""
+import ctypes as C
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1004_0480_amd", "csrc")
+
+
+def compile_host(tmp, name, source):
+    src, so = tmp / (name + ".cpp"), tmp / (name + ".so")
+    src.write_text(source)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), str(src), "-o", str(so)], check=True)
+    return C.CDLL(str(so))
+
+
+# ------------------------------------------------------- layout conversions
+
+@pytest.fixture(scope="module")
+def row_runs(tmp_path_factory):
+    lib = compile_host(tmp_path_factory.mktemp("io"), "io", """
+#include "rd_io_cfg.hpp"
+extern "C" void split(int64_t nx, int64_t rows, int64_t* out) {
+    const rdk::RowRuns r = rdk::row_runs(nx, rows);
+    const int64_t v[] = {r.run, r.parts, int64_t(r.blocks), r.deep};
+    for (int i = 0; i < 4; ++i) out[i] = v[i];
+}
+""")
+
+    def split(nx, rows):
+        out = (C.c_int64 * 4)()
+        lib.split(C.c_int64(nx), C.c_int64(rows), out)
+        return list(out)
+
+    return split
+
+
+def test_conversions_cover_every_unit_once(row_runs):
+    """The units that the workgroups of a conversion take (as the kernel forms
+    them) are the field's, each once."""
+    rng = random.Random(2)
+    shapes = [(1, 1), (5, 1), (4096, 1), (4097, 2), (9001, 3), (1 << 16, 1), (3, 5000), (403, 900)]
+    shapes += [(int(10 ** rng.uniform(0, 4.5)), int(10 ** rng.uniform(0, 2.5))) for _ in range(200)]
+    for nx, rows in shapes:
+        run, parts, blocks, _ = row_runs(nx, rows)
+        nx4, taken = (nx + 3) // 4, []
+        assert run == 1 or parts == 1
+        for b in range(blocks):
+            group, part = divmod(b, parts)
+            total = min(run, rows - group * run) * nx4
+            each = -(-total // parts)
+            taken += [group * run * nx4 + u for u in range(part * each, min((part + 1) * each, total))]
+        assert taken == list(range(rows * nx4)), (nx, rows)
+
+
+@pytest.mark.parametrize("nx,rows", [(1 << 24, 1), (1 << 22, 4), (1 << 18, 64), (1 << 24, 1 << 10)])
+def test_conversions_of_few_long_rows_fill_the_chip(row_runs, nx, rows):
+    assert row_runs(nx, rows)[2] >= 4 * 256       # workgroups: several for each compute unit
