@@ -61,3 +61,12 @@ def test_conversions_cover_every_unit_once(row_runs):
 @pytest.mark.parametrize("nx,rows", [(1 << 24, 1), (1 << 22, 4), (1 << 18, 64), (1 << 24, 1 << 10)])
 def test_conversions_of_few_long_rows_fill_the_chip(row_runs, nx, rows):
     assert row_runs(nx, rows)[2] >= 4 * 256       # workgroups: several for each compute unit
+
+
+@pytest.mark.parametrize("nx,rows", [(2052, 1 << 24), (4096, 1 << 24), (64, 1 << 34), (1 << 24, 1 << 16), (1, 1 << 40)])
+def test_conversions_of_the_largest_fields_fit_a_launch(row_runs, nx, rows):
+    """A launch holds fewer than 2^32 threads: 2^24 - 1 workgroups of 256."""
+    run, parts, blocks, _ = row_runs(nx, rows)
+    assert 0 < blocks < 1 << 24
+    assert -(-rows // run) * parts == blocks and (run == 1 or parts == 1)
+    assert run * -(-nx // 4) < 1 << 32                # a run's units are counted in 32 bits
