@@ -363,11 +363,11 @@ enum { RD_ROUND_NEAREST = 0, RD_ROUND_STOCHASTIC = 1 };
  * grids with stochastic rounding). */
 int rd_set_rounding(rd_grid *g, int32_t mode, uint64_t seed);
 
-/* Time candidate plans on this grid (trial_steps steps each, hipEvents on the
- * grid's stream), keep the fastest, store it in a per-process cache keyed by
- * shape, species, model and storage, and return it in *best.  The grid's state
- * is saved before and restored after, so the call leaves the fields as they
- * were.  Synchronous. */
+/* Time candidate plans on this grid (at least trial_steps steps each, in whole
+ * launches, hipEvents on the grid's stream), keep the fastest, store it in a
+ * per-process cache keyed by shape, species, model and storage, and return it
+ * in *best.  The grid's state is saved before and restored after, so the call
+ * leaves the fields as they were.  Synchronous. */
 int rd_autotune(rd_grid *g, int32_t trial_steps, rd_plan *best);
 
 /* ---------------------------------------------------------- batched form */

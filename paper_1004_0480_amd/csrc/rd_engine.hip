@@ -20,6 +20,7 @@
 #include "rd_march_cfg.hpp"
 #include "rd_internal.hpp"
 #include "rd_io.hpp"
+#include "rd_tune.hpp"
 
 using namespace rdk;
 
@@ -2123,15 +2124,17 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
     RD_HIP(hipEventCreate(&e1));
     rd_plan best_plan = heuristic_plan(g);
     int rc = RD_OK;
-    // time one plan over `steps` steps from the saved state and restore it;
-    // negative if the plan does not apply, rc set on a device error
+    // microseconds a step of one plan, over at least `steps` steps from the
+    // saved state, which is restored; negative if the plan does not apply, rc
+    // set on a device error
     auto time_plan = [&](const rd_plan& p, int steps) -> float {
         g->plan = p;
         if (apply_plan(g, true) != RD_OK) return -1.f;
         float ms = -1.f;
-        if ((rc = step_grid(g, 2)) != RD_OK) return -1.f;
+        const int per = steps_per_launch(g), n = tune_steps(steps, per);
+        if ((rc = step_grid(g, tune_warmup(per))) != RD_OK) return -1.f;
         if (hipEventRecord(e0, g->stream) != hipSuccess) { rc = fail(RD_EDEVICE, "event"); return -1.f; }
-        if ((rc = step_grid(g, steps + (steps & 1))) != RD_OK) return -1.f;
+        if ((rc = step_grid(g, n)) != RD_OK) return -1.f;
         if (hipEventRecord(e1, g->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
             rc = fail(RD_EDEVICE, "event sync failed");
             return -1.f;
@@ -2148,15 +2151,15 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
             return -1.f;
         }
         g->cur = cur0;
-        return ms;
+        return ms * 1e3f / float(n);
     };
     // every candidate once; then the four fastest twice more, over twice the
     // steps and in turn, so that near ties are settled by the longer runs
     std::vector<std::pair<float, rd_plan>> timed;
     for (const rd_plan& p : cands) {
-        const float ms = time_plan(p, trial_steps);
+        const float us = time_plan(p, trial_steps);
         if (rc) break;
-        if (ms >= 0.f) timed.push_back({ms, p});
+        if (us >= 0.f) timed.push_back({us, p});
     }
     if (rc == RD_OK && !timed.empty()) {
         std::stable_sort(timed.begin(), timed.end(),
@@ -2167,8 +2170,8 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
         std::vector<float> acc(top, 0.f);
         for (int rep = 0; rep < 2 && rc == RD_OK; ++rep)
             for (size_t i = 0; i < top && rc == RD_OK; ++i) {
-                const float ms = time_plan(timed[i].second, 2 * trial_steps);
-                acc[i] += ms >= 0.f ? ms : 1e30f;
+                const float us = time_plan(timed[i].second, 2 * trial_steps);
+                acc[i] += us >= 0.f ? us : 1e30f;
             }
         size_t bi = 0;
         for (size_t i = 1; i < top; ++i)

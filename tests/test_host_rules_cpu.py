@@ -70,3 +70,25 @@ def test_conversions_of_the_largest_fields_fit_a_launch(row_runs, nx, rows):
     assert 0 < blocks < 1 << 24
     assert -(-rows // run) * parts == blocks and (run == 1 or parts == 1)
     assert run * -(-nx // 4) < 1 << 32                # a run's units are counted in 32 bits
+
+
+# --------------------------------------------------------------- autotuning
+
+@pytest.fixture(scope="module")
+def tune(tmp_path_factory):
+    lib = compile_host(tmp_path_factory.mktemp("tune"), "tune", """
+#include "rd_tune.hpp"
+extern "C" int steps(int trial, int per) { return rdk::tune_steps(trial, per); }
+extern "C" int warmup(int per) { return rdk::tune_warmup(per); }
+""")
+    return lib
+
+
+def test_candidates_are_timed_over_whole_launches(tune):
+    """No left-over launch is timed, whatever the trial count, and a plan's own
+    kernel has run before the first timed launch."""
+    for per in (1, 2, 3, 4):
+        assert tune.warmup(per) >= per
+        for trial in range(1, 40):
+            n = tune.steps(trial, per)
+            assert n % per == 0 and n % 2 == 0 and trial <= n < trial + 2 * per
