@@ -171,7 +171,7 @@ enum {
                               7-point models, and for 19-point ones the first
                               LDS-ring shape, with z chunks for about two
                               workgroups per CU.  A register-march plan that was
-                              set by name gives way to the heuristic while the
+                              set by name gives way to this choice while the
                               model or rounding is one it does not take         */
     RD_KERNEL_DIRECT = 1,  /* one thread per cell, neighbours through the cache */
     RD_KERNEL_TILED = 2,   /* xy tile per workgroup, z-march register window,
@@ -365,8 +365,10 @@ int rd_set_rounding(rd_grid *g, int32_t mode, uint64_t seed);
 
 /* Time candidate plans on this grid (at least trial_steps steps each, in whole
  * launches, hipEvents on the grid's stream), keep the fastest, store it in a
- * per-process cache keyed by shape, species, model and storage, and return it
- * in *best.  The grid's state is saved before and restored after, so the call
+ * per-process cache keyed by shape, species, model, storage and whether a
+ * register march takes the grid (its faces and rounding), and return it in
+ * *best; the fastest plan of the other kinds is kept for grids that no march
+ * takes, until one of them is tuned.  The grid's state is saved before and restored after, so the call
  * leaves the fields as they were.  Synchronous. */
 int rd_autotune(rd_grid *g, int32_t trial_steps, rd_plan *best);
 

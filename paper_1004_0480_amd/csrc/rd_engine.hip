@@ -762,19 +762,24 @@ bool march19_plan(const rd_grid* g, int steps, int lanes, rd_plan* out) {
     return best < 1e300;
 }
 
-rd_plan heuristic_plan(const rd_grid* g) {
+// The default plan; *march: whether a register march takes the grid.
+rd_plan heuristic_plan(const rd_grid* g, bool* march = nullptr) {
     rd_plan best{};
     best.kernel = RD_KERNEL_DIRECT;
+    const bool takes = g->model == RD_MODEL_FRONT_CH ? fmarch_plan(g, -1, &best)
+                       : g->args[0][0].s19           ? march19_plan(g, 0, 0, &best)
+                                                     : march_plan(g, -1, &best);
+    if (march) *march = takes;
     // The register march wherever it applies: on every grid measured it beat
     // the slab this rule chose before, and the best of the other plans
     // (us per step, FP32: diffusion 512^3 77 against 189, Brusselator 256^3 28
     // against 44, pollutant 512x512x128 131 against 218, diffusion 64^3 2.5
-    // against 6.1).
-    if (g->model != RD_MODEL_FRONT_CH && march_plan(g, -1, &best)) return best;
-    // and its front form, against the one-pass LDS form this rule chose before
-    // (us per step: 384x384x512 FP32 376 against 420, BF16 232 against 383;
-    // 248x200x180 42 against 62 and 29 against 65; 64^3 8.4 against 26)
-    if (g->model == RD_MODEL_FRONT_CH && fmarch_plan(g, -1, &best)) return best;
+    // against 6.1); its front form against the one-pass LDS form (384x384x512
+    // FP32 376 against 420, BF16 232 against 383; 248x200x180 42 against 62 and
+    // 29 against 65; 64^3 8.4 against 26); its 19-point form against the ring or
+    // direct plan chosen below (Turing FP32 192^3 20.8 and 44.5, 256^3 42.4 and
+    // 67.8 (tuned ring 46.6), 130x101x77 8.5 and 59.6, 32^3 5.2 and 6.8)
+    if (takes) return best;
     if (g->model == RD_MODEL_FRONT_CH && !g->args[0][0].s19) {
         // the one-pass front kernel, its largest shape for this storage
         for (int i = 0; i < kNumFchCfgs; ++i) {
@@ -792,10 +797,6 @@ rd_plan heuristic_plan(const rd_grid* g) {
         }
     }
     if (g->args[0][0].s19) {
-        // the 19-point march wherever it applies (us per step of Turing FP32
-        // against the ring or direct plan chosen below: 192^3 20.8 and 44.5,
-        // 256^3 42.4 and 67.8 (tuned ring 46.6), 130x101x77 8.5 and 59.6, 32^3 5.2 and 6.8)
-        if (march19_plan(g, 0, 0, &best)) return best;
         // 19-point: the first LDS-ring shape this grid and model take, with
         // z chunks that give about two workgroups per CU; else direct
         for (int i = 0; i < kNumLdsCfgs; ++i) {
@@ -819,11 +820,11 @@ rd_plan heuristic_plan(const rd_grid* g) {
     return slab_plan(g);
 }
 std::mutex g_tune_mu;
-// autotuned plans by (nx, ny, nz, species, model, stencil and integrator, storage)
-std::map<std::tuple<int64_t, int64_t, int64_t, int, int, int>, rd_plan> g_tune_cache;
+PlanCache g_tune_cache;      // autotuned plans of this process
 int tune_model_key(const rd_grid* g) {
     return (g->model * 2 + (g->args[0][0].s19 ? 1 : 0)) * 4 + g->integrator;
 }
+PlanCache::Key tune_key(const rd_grid* g) { return {g->nx, g->ny, g->nz, g->ns, tune_model_key(g), g->storage}; }
 
 int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
     if (p.graph_chunk != 0 && (p.graph_chunk < 2 || (p.graph_chunk & 1)))
@@ -982,25 +983,25 @@ bool one_pass(const rd_grid* g) {
 // A register-march plan takes fewer integrators, roundings and faces than the
 // plans that autotuning found before it: `named` (rd_set_plan) refuses one that
 // does not fit, but one that was set and ceases to fit by a later setting gives
-// way to the heuristic plan for as long as it does.
+// way to the plan that the library would choose for as long as it does.
 int apply_plan(rd_grid* g, bool named = false) {
     rd_plan p = g->plan;
     int cfg = -1;
-    if (!named && is_march(p) && check_plan(g, p, &cfg) != RD_OK) {
-        const int gc = p.graph_chunk;
-        p = heuristic_plan(g);
-        p.graph_chunk = gc;
-    }
+    if (!named && is_march(p) && check_plan(g, p, &cfg) != RD_OK) p.kernel = RD_KERNEL_AUTO;
     if (p.kernel == RD_KERNEL_AUTO) {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_tune_cache.find({g->nx, g->ny, g->nz, g->ns, tune_model_key(g), g->storage});
         const int gc = p.graph_chunk;
-        p = it != g_tune_cache.end() ? it->second : heuristic_plan(g);
+        bool march = false;
+        const rd_plan h = heuristic_plan(g, &march);
+        {
+            std::lock_guard<std::mutex> lk(g_tune_mu);
+            const rd_plan* tuned = g_tune_cache.get(tune_key(g), march);
+            p = tuned ? *tuned : h;
+        }
         p.graph_chunk = gc;
         // a cached plan this grid cannot take (other settings since it was
         // tuned) gives way to the heuristic one
         if (check_plan(g, p, &cfg) != RD_OK) {
-            p = heuristic_plan(g);
+            p = h;
             p.graph_chunk = gc;
         }
     }
@@ -2122,7 +2123,8 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
     hipEvent_t e0, e1;
     RD_HIP(hipEventCreate(&e0));
     RD_HIP(hipEventCreate(&e1));
-    rd_plan best_plan = heuristic_plan(g);
+    bool march = false;                    // a grid that a register march takes
+    rd_plan best_plan = heuristic_plan(g, &march), general{};   // the fastest, and the fastest that is no march
     int rc = RD_OK;
     // microseconds a step of one plan, over at least `steps` steps from the
     // saved state, which is restored; negative if the plan does not apply, rc
@@ -2177,6 +2179,12 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
         for (size_t i = 1; i < top; ++i)
             if (acc[i] < acc[bi]) bi = i;
         if (rc == RD_OK) best_plan = timed[bi].second;
+        // (of the plans that are no march, the longer runs decide between those
+        // among the four)
+        size_t gi = timed.size();
+        for (size_t i = timed.size(); i-- > 0;)
+            if (!is_march(timed[i].second) && (i >= top || gi >= top || acc[i] < acc[gi])) gi = i;
+        if (gi < timed.size()) general = timed[gi].second;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -2190,7 +2198,7 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
     if (rc == RD_OK) {
         best_plan.graph_chunk = 0;
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune_cache[{g->nx, g->ny, g->nz, g->ns, tune_model_key(g), g->storage}] = best_plan;
+        g_tune_cache.put(tune_key(g), march, best_plan, general.kernel != RD_KERNEL_AUTO ? &general : nullptr);
     }
     g->plan = user;
     const int rc2 = apply_plan(g);

@@ -268,3 +268,32 @@ def test_march19_plans_bitwise(model, storage):
             for plan in plans:
                 got, _ = run(spec, shape, f, storage, [2, 3], dict(plan, kernel="lds"))
                 assert same(got, ref), (model, shape, name, plan)
+
+
+def test_tuning_one_class_of_faces_leaves_the_other_its_plans():
+    """Autotuning a grid whose faces no register march takes does not keep grids
+    of its shape from theirs, nor the other way round; and a tuned march that
+    gives way to a rounding it does not take is followed by a plan that does."""
+    mirror = FACES["mirror"]
+    for first, shape in (("held", (22, 26, 68)), ("mirror", (24, 26, 68))):
+        spec = {"held": spec_of("brusselator", shape, (HELD,) + mirror[1:]), "mirror": spec_of("brusselator", shape, mirror)}
+        f = fields_of(shape, 2, 4)
+        used = {}
+        for name in (first, "mirror" if first == "held" else "held"):
+            g = rd.Grid(shape, 2, 1.0, "bf16")
+            g.set_model(spec[name])
+            for s, x in enumerate(f):
+                g.write(s, x)
+            if name == first:
+                g.set_plan(**dict(g.autotune(4), graph_chunk=0))
+            used[name] = g.plan()
+            g.step(5)
+            got = g.read_all(np.float32)
+            assert same(got, run(spec[name], shape, f, "bf16", [5], dict(kernel="direct"))[0])
+            if name == first == "mirror":
+                g.set_rounding("stochastic", 3)
+                assert g.plan()["kernel"] != 8
+            g.close()
+        assert used["held"]["kernel"] != 8
+        if first == "held":
+            assert used["mirror"]["kernel"] == 8

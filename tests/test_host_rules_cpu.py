@@ -80,6 +80,17 @@ def tune(tmp_path_factory):
 #include "rd_tune.hpp"
 extern "C" int steps(int trial, int per) { return rdk::tune_steps(trial, per); }
 extern "C" int warmup(int per) { return rdk::tune_warmup(per); }
+static rdk::PlanCache cache;
+static rdk::PlanCache::Key key(int n) { return {n, n, n, 1, 0, 0}; }
+extern "C" void put(int n, int march, int best, int general) {
+    rd_plan b{}, g{};
+    b.kernel = best, g.kernel = general;
+    cache.put(key(n), march != 0, b, general ? &g : nullptr);
+}
+extern "C" int get(int n, int march) {
+    const rd_plan* p = cache.get(key(n), march != 0);
+    return p ? p->kernel : 0;
+}
 """)
     return lib
 
@@ -92,3 +103,20 @@ def test_candidates_are_timed_over_whole_launches(tune):
         for trial in range(1, 40):
             n = tune.steps(trial, per)
             assert n % per == 0 and n % 2 == 0 and trial <= n < trial + 2 * per
+
+
+def test_tuned_plans_serve_their_own_class_of_grids(tune):
+    """A shape's tuned register march is not what a grid that no march takes is
+    given, and a tuned ring is not what keeps a grid from its march."""
+    march, ring, tring, lds = 8, 4, 7, 5
+    tune.put(1, 0, ring, ring)                 # a grid with held faces, tuned alone
+    assert tune.get(1, 0) == ring and tune.get(1, 1) == 0
+    tune.put(2, 1, march, ring)                # a march's grid: its best other plan serves the rest
+    assert tune.get(2, 1) == march and tune.get(2, 0) == ring
+    tune.put(2, 0, tring, tring)               # which are then tuned themselves, and keep that
+    tune.put(2, 1, lds, lds)                   # (another plan may beat the march on its own grid)
+    assert tune.get(2, 0) == tring and tune.get(2, 1) == lds
+    tune.put(3, 1, march, 0)                   # none but marches ran
+    assert tune.get(3, 0) == 0 and tune.get(4, 0) == tune.get(4, 1) == 0
+    tune.put(3, 1, march, ring)
+    assert tune.get(3, 0) == ring
