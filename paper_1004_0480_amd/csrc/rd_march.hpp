@@ -54,6 +54,7 @@
 #pragma once
 
 #include "rd_march_cfg.hpp"
+#include "rd_tiles.hpp"
 
 namespace rdk {
 
@@ -584,22 +585,10 @@ __global__ __launch_bounds__(64 * W) void march_kernel(const StepArgs* __restric
     const bool left_over = a.mg[MG_STEPS] != K;
     const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz, chunks = left_over ? a.mg[MG_LEFT_CHUNKS] : a.chunks_z;
     const int tiles_y = (a.ny + by - 1) / by;
-    int b = xcd_tile(blockIdx.x, gridDim.x);
-    int tx, ty, tz;
-    if (a.zfast) {
-        tz = b % chunks;
-        b /= chunks;
-        tx = b % a.tiles_x;
-        ty = b / a.tiles_x;
-    } else {
-        tx = b % a.tiles_x;
-        b /= a.tiles_x;
-        ty = b % tiles_y;
-        tz = b / tiles_y;
-    }
-    const int z0 = tz * cz;
-    march_tile_steps<M, S, RY, W, K, K, XEX, RAG, MIR>(a, (RD_LDS float*)&rows_s[0], (RD_LDS float*)&edge_s[0], tx,
-                                                       ty * by, z0, min(z0 + cz, a.nz));
+    const MarchTile t = march_tile(xcd_tile(blockIdx.x, gridDim.x), a.tiles_x, tiles_y, chunks, a.zfast != 0);
+    const int z0 = t.z * cz;
+    march_tile_steps<M, S, RY, W, K, K, XEX, RAG, MIR>(a, (RD_LDS float*)&rows_s[0], (RD_LDS float*)&edge_s[0], t.x,
+                                                       t.y * by, z0, min(z0 + cz, a.nz));
 }
 
 // The batched form (served grids of diffusion or the Brusselator): a persistent

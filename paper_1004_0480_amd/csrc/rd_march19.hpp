@@ -40,16 +40,14 @@ __global__ __launch_bounds__(64 * W) void march19_kernel(const StepArgs* __restr
     // ---- the tile ---------------------------------------------------------
     const int L = a.mg[MG_LANES], halo = a.mg[MG_HALO], G = T / L, BY = G - 2 * K;
     const bool left_over = a.mg[MG_STEPS] != K;
-    const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz;
+    const int cz = left_over ? a.mg[MG_LEFT_CZ] : a.cz, chunks = left_over ? a.mg[MG_LEFT_CHUNKS] : a.chunks_z;
     const int tiles_y = (a.ny + BY - 1) / BY;
-    int b = xcd_tile(blockIdx.x, gridDim.x);
-    const int tx = b % a.tiles_x;
-    b /= a.tiles_x;
-    const int yb = b % tiles_y * BY, z0 = b / tiles_y * cz, z1 = min(z0 + cz, a.nz);
+    const MarchTile tile = march_tile(xcd_tile(blockIdx.x, gridDim.x), a.tiles_x, tiles_y, chunks, a.zfast != 0);
+    const int yb = tile.y * BY, z0 = tile.z * cz, z1 = min(z0 + cz, a.nz);
     const int yg = t / L, x4 = t - yg * L;
     const bool perx = a.bck[0][0] == BC_PERIODIC, pery = a.bck[0][2] == BC_PERIODIC,
                perz = a.bck[0][4] == BC_PERIODIC;
-    const int x = (tx * (L - 2 * halo) + x4 - halo) * 4;
+    const int x = (tile.x * (L - 2 * halo) + x4 - halo) * 4;
     int xm = x;
     if (perx && halo) xm = x < 0 ? x + a.nx : x >= a.nx ? x - a.nx : x;
     xm = min(max(xm, 0), a.pitch - 4);

@@ -297,3 +297,27 @@ def test_tuning_one_class_of_faces_leaves_the_other_its_plans():
         assert used["held"]["kernel"] != 8
         if first == "held":
             assert used["mirror"]["kernel"] == 8
+
+
+def test_march19_orders_bitwise():
+    """Both tile orders of the 19-point march, with left-over launches, on grids
+    of several tiles along every axis."""
+    for shape in ((13, 70, 300), (21, 65, 57), (9, 40, 64)):
+        spec = W.turing_spec()
+        f = fields_of(shape, 2, 12)
+        ref, _ = run(spec, shape, f, "f32", [5], dict(kernel="direct"))
+        g = rd.Grid(shape, 2, spec.h, "f32")
+        g.set_model(spec)
+        plans = []
+        for k in (1, 2):
+            for ry in range(1, 33):
+                try:
+                    g.set_plan(kernel="lds", vx=0, ry=ry, waves=8, prefetch=k, cz=4, order=1)
+                    plans.append(g.plan())
+                except rd.RDError as e:
+                    assert e.code == rd.EINVAL
+        g.close()
+        assert {p["prefetch"] for p in plans} == {1, 2} and all(p["order"] == 1 for p in plans)
+        for plan in plans:
+            got, _ = run(spec, shape, f, "f32", [2, 3], dict(plan, kernel="lds"))
+            assert same(got, ref), (shape, plan)

@@ -120,3 +120,35 @@ def test_tuned_plans_serve_their_own_class_of_grids(tune):
     assert tune.get(3, 0) == 0 and tune.get(4, 0) == tune.get(4, 1) == 0
     tune.put(3, 1, march, ring)
     assert tune.get(3, 0) == ring
+
+
+# ------------------------------------------------------------ tiles of a march
+
+def test_march_tiles_in_both_orders(tmp_path):
+    """Every tile once in either order: x, then y, then the z chunk, or the z
+    chunk first."""
+    lib = compile_host(tmp_path, "tiles", """
+#include "rd_tiles.hpp"
+extern "C" void tile(int b, int x, int y, int z, int zfast, int* out) {
+    const rdk::MarchTile t = rdk::march_tile(b, x, y, z, zfast != 0);
+    out[0] = t.x, out[1] = t.y, out[2] = t.z;
+}
+""")
+    out = (C.c_int * 3)()
+    for nx, ny, nz in ((1, 1, 1), (3, 5, 7), (1, 4, 2), (6, 1, 9)):
+        for zfast in (0, 1):
+            got = []
+            for b in range(nx * ny * nz):
+                lib.tile(b, nx, ny, nz, zfast, out)
+                got.append(tuple(out))
+            want = ([(x, y, z) for y in range(ny) for x in range(nx) for z in range(nz)] if zfast else
+                    [(x, y, z) for z in range(nz) for y in range(ny) for x in range(nx)])
+            assert got == want
+
+
+def test_every_march_kernel_takes_its_plan_order():
+    """A plan's order reaches the march kernels: each forms its tile with the
+    shared rule, from the arguments' order (the 19-point march ignored it)."""
+    for name in ("rd_march.hpp", "rd_march19.hpp"):
+        with open(os.path.join(CSRC, name)) as fh:
+            assert "march_tile(xcd_tile(blockIdx.x, gridDim.x), a.tiles_x, tiles_y, chunks, a.zfast != 0)" in fh.read()
