@@ -321,3 +321,49 @@ def test_march19_orders_bitwise():
         for plan in plans:
             got, _ = run(spec, shape, f, "f32", [2, 3], dict(plan, kernel="lds"))
             assert same(got, ref), (shape, plan)
+
+
+def check_single_steps_of_a_large_field(spec, shape, stencil_march):
+    """A grid whose buffers pass the last cache (256 MB), by default plan: calls
+    that leave one step, directly and in graphs, from both parities; then a
+    Runge-Kutta model on the same grid, whose stage arguments the left-over
+    launch borrows."""
+    import torch
+    rng = np.random.default_rng(8)
+    f = [(rng.random(shape, dtype=np.float32) + np.float32(0.5)) for _ in range(spec.ns)]
+    rk = W.ModelSpec(**dict(vars(spec), integrator="rk2"))
+
+    def sequence(plan, chunk):
+        g = rd.Grid(shape, spec.ns, spec.h, "f32", stream=torch.cuda.Stream())
+        g.set_model(spec)
+        g.set_plan(**dict(plan, graph_chunk=chunk))
+        used = g.plan()
+        for s, x in enumerate(f):
+            g.write(s, x)
+        out = []
+        for n in (1, 2, 5, 1):
+            g.step(n)
+            out.append([x[::7].copy() for x in g.read_all(np.float32)])
+        g.set_model(rk)
+        g.step(3)
+        out.append(g.read_all(np.float32))
+        g.set_model(spec)
+        g.step(3)
+        out.append(g.read_all(np.float32))
+        g.close()
+        return out, used
+
+    ref, _ = sequence(dict(kernel="direct"), 0)
+    for chunk in (0, 2, 6):
+        got, used = sequence(dict(kernel="auto"), chunk)
+        assert (used["kernel"], used["vx"]) == ((rd.KERNEL["lds"], 0) if stencil_march else (rd.KERNEL["march"], 4))
+        for i, (a, b) in enumerate(zip(got, ref)):
+            assert same(a, b), (chunk, i)
+
+
+@pytest.mark.parametrize("model", ["diffusion", "pollutant1"])
+def test_single_steps_of_a_large_field(model):
+    shape = (322, 280, 330)
+    assert 2 * 384 * shape[0] * shape[1] * 4 > 256 << 20
+    check_single_steps_of_a_large_field(spec_of(model, shape, FACES["ghost_lo" if model != "diffusion" else "mirror"]), shape,
+                                        False)
