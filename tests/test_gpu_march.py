@@ -367,3 +367,28 @@ def test_single_steps_of_a_large_field(model):
     assert 2 * 384 * shape[0] * shape[1] * 4 > 256 << 20
     check_single_steps_of_a_large_field(spec_of(model, shape, FACES["ghost_lo" if model != "diffusion" else "mirror"]), shape,
                                         False)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_march_tables_of_long_chunks(storage):
+    """A march looks the wind and the source planes up 64 planes at a time: one
+    chunk over all planes, with sources on both sides of every refill, on the
+    planes next to the faces and in between."""
+    for nz in (62, 63, 64, 65, 66, 130):
+        shape = (nz, 9, 40)
+        zs = sorted(z for z in {0, 1, 2, 31, 59, 60, 61, 62, 63, 64, 65, 66, 67, 123, 124, 125, 126, 127, 128, 129, nz - 2, nz - 1}
+                    if z < nz)
+        rng = np.random.default_rng(nz)
+        cells = np.array([(z * 9 + rng.integers(9)) * 40 + rng.integers(40) for z in zs for _ in range(2)], dtype=np.int64)
+        for model, plans in (("pollutant1", [(1, 8, 2), (1, 8, 3), (1, 16, 3), (1, 8, 4)]), ("pollutant4", [(1, 8, 2), (2, 8, 2)])):
+            for name in ("mirror", "periodic"):
+                spec = spec_of(model, shape, FACES[name])
+                spec.sources = (cells, (np.arange(len(cells)) % spec.ns).astype(np.int32), 1.0 + np.arange(len(cells)) / 8.0)
+                spec.wind = np.linspace(0.1, 4.0, nz)
+                f = fields_of(shape, spec.ns, nz)
+                ref, _ = run(spec, shape, f, storage, [9], dict(kernel="direct"))
+                for ry, w, k in plans:
+                    for cz in (0, 61):
+                        plan = dict(kernel="march", vx=4, ry=ry, waves=w, prefetch=k, cz=cz)
+                        got, used = run(spec, shape, f, storage, [9], plan)
+                        assert used["kernel"] == 8 and same(got, ref), (nz, model, name, plan)
