@@ -309,7 +309,7 @@ struct rd_grid {
     int cfg = -1;
     long long blocks[2] = {0, 0};
     int march_rows = 0;                // register march: rows of a tile, its halo included
-    int left_cfg = -1;                 // its slab shape for single steps (-1: the march's own)
+    int left_kernel = 0, left_cfg = -1; // its plan kind and shape for single steps (-1: the march's own)
     long long left_blocks = 0;
     int variant = 0;                   // register march: MARCH_*
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
@@ -383,6 +383,11 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
         }
     }
     return best;
+}
+
+// Both states of a grid together pass the last cache (256 MB).
+bool beyond_cache(const rd_grid* g) {
+    return 2 * g->ns * g->plane * g->nz * (long long)(elem_size(g->storage)) > (256LL << 20);
 }
 
 // The one-pass front plan in its register-march form.
@@ -699,6 +704,29 @@ rd_plan slab_plan(const rd_grid* g) {
     return best;
 }
 
+// The first LDS-ring shape a 19-point grid and its model take, with z chunks
+// that give about two workgroups per CU; false if there is none.
+bool ring_plan(const rd_grid* g, rd_plan* out) {
+    for (int i = 0; i < kNumLdsCfgs; ++i) {
+        const LdsCfg c = kLdsCfgs[i];
+        bool ok = ring_row_fits(g, c.nch);
+        for (int k = 0; k < g->npass; ++k) ok = ok && lds_ok(g->storage, g->pass_pm[k], i);
+        if (!ok) continue;
+        *out = rd_plan{};
+        out->kernel = RD_KERNEL_LDS;
+        out->vx = 4 * c.nch;
+        out->ry = c.by;
+        out->waves = c.wc;
+        out->prefetch = c.d;
+        const int yblocks = (g->ny + c.by - 1) / c.by;
+        const int chunks = std::max(1, 2 * num_cus() / yblocks);
+        const int cz = (g->nz + chunks - 1) / chunks;
+        out->cz = cz < g->nz ? cz : 0;
+        return true;
+    }
+    return false;
+}
+
 // The register-march shape (-1: any) and chunk length of least predicted time
 // per step; false if no shape takes the grid and its model.
 bool march_plan(const rd_grid* g, int shape, rd_plan* out) {
@@ -797,24 +825,7 @@ rd_plan heuristic_plan(const rd_grid* g, bool* march = nullptr) {
         }
     }
     if (g->args[0][0].s19) {
-        // 19-point: the first LDS-ring shape this grid and model take, with
-        // z chunks that give about two workgroups per CU; else direct
-        for (int i = 0; i < kNumLdsCfgs; ++i) {
-            const LdsCfg c = kLdsCfgs[i];
-            bool ok = ring_row_fits(g, c.nch);
-            for (int k = 0; k < g->npass; ++k) ok = ok && lds_ok(g->storage, g->pass_pm[k], i);
-            if (!ok) continue;
-            best.kernel = RD_KERNEL_LDS;
-            best.vx = 4 * c.nch;
-            best.ry = c.by;
-            best.waves = c.wc;
-            best.prefetch = c.d;
-            const int yblocks = (g->ny + c.by - 1) / c.by;
-            const int chunks = std::max(1, 2 * num_cus() / yblocks);
-            const int cz = (g->nz + chunks - 1) / chunks;
-            best.cz = cz < g->nz ? cz : 0;
-            break;
-        }
+        (void)ring_plan(g, &best);      // else direct
         return best;
     }
     return slab_plan(g);
@@ -1029,21 +1040,26 @@ int apply_plan(rd_grid* g, bool named = false) {
                 g->blocks[k] = 0;
             }
         }
-    // One step of a large FP32 field alone moves as many bytes in a march as in
-    // the slabs, and more in its halos: beyond the 256 MB of the last cache the
-    // slabs are the faster single step (diffusion 512^3: 210 against 238 us;
-    // 256^3, within the cache: 26 against 24).  Their arguments take the place
-    // of the Runge-Kutta stage's, which such a plan has no use for.
+    // One step of large FP32 fields alone moves as many bytes in a march as in
+    // the other plans, and more in its halos: beyond the 256 MB of the last cache
+    // those are the faster single step for one field (slab; diffusion 512^3: 210
+    // against 238 us; 256^3, within the cache: 26 against 24) and in the 19-point
+    // form (LDS ring; Turing 512x512x256: 220 against 309 us, diffusion 512^3 204
+    // against 328; two fields of the 7-point form were no slower in a march, nor
+    // 16-bit ones).  Their arguments take the place of the Runge-Kutta stage's,
+    // which such a plan has no use for.
     g->left_cfg = -1;
-    if (p.kernel == RD_KERNEL_MARCH && g->npass == 1 && g->storage == RD_F32 &&
-        march_fields(g->pass_pm[0]) == 1 && 2 * g->plane * g->nz * 4 > (256LL << 20)) {
-        const rd_plan sp = slab_plan(g);
+    if (g->npass == 1 && g->storage == RD_F32 && beyond_cache(g)) {
+        rd_plan lp{};
+        if (p.kernel == RD_KERNEL_MARCH && march_fields(g->pass_pm[0]) == 1) lp = slab_plan(g);
+        else if (is_march19(p)) (void)ring_plan(g, &lp);
         int c = -1;
-        if (sp.kernel == RD_KERNEL_BLOCK && check_plan(g, sp, &c) == RD_OK) {
+        if ((lp.kernel == RD_KERNEL_BLOCK || lp.kernel == RD_KERNEL_LDS) && check_plan(g, lp, &c) == RD_OK) {
             for (int par = 0; par < 2; ++par) {
                 g->rk_args[par][0] = g->args[par][0];
-                g->left_blocks = set_tiling(g->rk_args[par][0], sp);
+                g->left_blocks = set_tiling(g->rk_args[par][0], lp);
             }
+            g->left_kernel = lp.kernel;
             if (g->left_blocks <= 0x7fffffffLL) g->left_cfg = c;
         }
     }
@@ -1153,7 +1169,7 @@ int launch_left(rd_grid* g, int parity, int64_t n, int* rc) {
     if (several_steps(g)) {
         const int steps = n >= 2 && g->eff.prefetch > 2 ? 2 : 1;
         if (steps == 1 && g->left_cfg >= 0) {
-            const hipError_t e = launch_pass(g->storage, g->pass_pm[0], RD_KERNEL_BLOCK, g->left_cfg,
+            const hipError_t e = launch_pass(g->storage, g->pass_pm[0], g->left_kernel, g->left_cfg,
                                              g->rk_args[parity][0], g->d_args + 4 + parity * 2, g->left_blocks,
                                              g->stream);
             *rc = e == hipSuccess ? RD_OK : fail(RD_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));

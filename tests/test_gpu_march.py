@@ -392,3 +392,13 @@ def test_march_tables_of_long_chunks(storage):
                         plan = dict(kernel="march", vx=4, ry=ry, waves=w, prefetch=k, cz=cz)
                         got, used = run(spec, shape, f, storage, [9], plan)
                         assert used["kernel"] == 8 and same(got, ref), (nz, model, name, plan)
+
+
+@pytest.mark.parametrize("model", ["diffusion", "turing"])
+def test_single_steps_of_a_large_19_point_field(model):
+    shape = {"diffusion": (300, 300, 384), "turing": (152, 300, 384)}[model]
+    spec = spec_of(model, shape, FACES["mirror"])
+    spec.stencil = 19
+    spec.K = [[max(k)] * 3 for k in spec.K]
+    assert 2 * spec.ns * 384 * shape[0] * shape[1] * 4 > 256 << 20
+    check_single_steps_of_a_large_field(spec, shape, True)
