@@ -56,6 +56,7 @@ size_t field_elems(int64_t nx, int64_t ny, int64_t nz) {
     return size_t(pitch_of(nx)) * size_t(ny) * size_t(nz) + SLACK;
 }
 bool is_finite(double v) { return std::isfinite(v); }
+constexpr long long kLastCache = 256LL << 20;   // bytes of the last cache
 
 // Species of a single-field-group model split into passes that share no
 // term, so that each pass carries few fields: the pollutant's coupled pair
@@ -385,9 +386,9 @@ MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
     return best;
 }
 
-// Both states of a grid together pass the last cache (256 MB).
+// Both states of a grid together pass the last cache.
 bool beyond_cache(const rd_grid* g) {
-    return 2 * g->ns * g->plane * g->nz * (long long)(elem_size(g->storage)) > (256LL << 20);
+    return 2 * g->ns * g->plane * g->nz * (long long)(elem_size(g->storage)) > kLastCache;
 }
 
 // The one-pass front plan in its register-march form.
@@ -500,12 +501,18 @@ double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m,
     return march_cost(k, c.ry, c.w, m, nx, ny, nz, cz);
 }
 
-// The 19-point march.
+// The 19-point march.  Its plane takes longer where the fields come from memory:
+// with 0.9 us throughout (and 23 instructions for one field) long chunks of one
+// step a launch were predicted fastest for one large 16-bit field: diffusion BF16
+// 512^3 198 us a step, two steps a launch 106, 256x328x888 88 and 68; over 14
+// grids and all their plans the predicted best was 5.8 % off the measured on
+// average and up to 54 %, with these constants 3.1 and 17 %.
 double march19_time(int storage, int pm, int k, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz, int cz) {
     const int nf = march19_fields(pm);
+    const bool cached = 2.0 * nf * pitch_of(nx) * double(ny) * double(nz) * double(elem_size(storage)) <= double(kLastCache);
     MarchCost c{};
-    c.instr = (nf == 1 ? 23.0 : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
-    c.latency = 0.9, c.launch = 1.4, c.fill = 0.5;
+    c.instr = (nf == 1 ? 20.0 : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
+    c.latency = cached ? 0.9 : 1.2, c.launch = 1.4, c.fill = 0.5;
     c.tbs = 5.96, c.halo_xy = 0.65, c.halo_z = 0.66;
     c.halo = k;
     c.extra = 3 * k - 1;
