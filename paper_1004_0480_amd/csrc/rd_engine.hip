@@ -1047,19 +1047,24 @@ int apply_plan(rd_grid* g, bool named = false) {
                 g->blocks[k] = 0;
             }
         }
-    // One step of large FP32 fields alone moves as many bytes in a march as in
-    // the other plans, and more in its halos: beyond the 256 MB of the last cache
-    // those are the faster single step for one field (slab; diffusion 512^3: 210
-    // against 238 us; 256^3, within the cache: 26 against 24) and in the 19-point
-    // form (LDS ring; Turing 512x512x256: 220 against 309 us, diffusion 512^3 204
-    // against 328; two fields of the 7-point form were no slower in a march, nor
-    // 16-bit ones).  Their arguments take the place of the Runge-Kutta stage's,
-    // which such a plan has no use for.
+    // One step of large fields alone moves as many bytes in a march as in the
+    // other plans, and more in its halos.  Beyond the last cache those are the
+    // faster single step for one FP32 field (slab; diffusion 512^3: 210 against
+    // 238 us; 256^3, within the cache: 26 against 24) and in the 19-point form for
+    // FP32 or one field (LDS ring; FP32 Turing 512x512x256 220 against 309 us,
+    // diffusion 512^3 204 against 328, BF16 148 against 179; Turing 384^3 BF16 214
+    // against 139).  Two fields of the 7-point form were no slower in a march.
+    // Their arguments take the place of the Runge-Kutta stage's, which such a
+    // plan has no use for.
     g->left_cfg = -1;
-    if (g->npass == 1 && g->storage == RD_F32 && beyond_cache(g)) {
+    if (g->npass == 1 && beyond_cache(g)) {
         rd_plan lp{};
-        if (p.kernel == RD_KERNEL_MARCH && march_fields(g->pass_pm[0]) == 1) lp = slab_plan(g);
-        else if (is_march19(p)) (void)ring_plan(g, &lp);
+        const bool f32 = g->storage == RD_F32;
+        if (p.kernel == RD_KERNEL_MARCH && f32 && march_fields(g->pass_pm[0]) == 1) lp = slab_plan(g);
+        // (16-bit rows have to fill the ring's: 384x384x512, rows of 512, 121 against 89)
+        else if (is_march19(p) && ring_plan(g, &lp) &&
+                 !(f32 || (march19_fields(g->pass_pm[0]) == 1 && 8 * g->nx >= 7 * 64 * lp.vx)))
+            lp = rd_plan{};
         int c = -1;
         if ((lp.kernel == RD_KERNEL_BLOCK || lp.kernel == RD_KERNEL_LDS) && check_plan(g, lp, &c) == RD_OK) {
             for (int par = 0; par < 2; ++par) {

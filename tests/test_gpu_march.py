@@ -323,7 +323,7 @@ def test_march19_orders_bitwise():
             assert same(got, ref), (shape, plan)
 
 
-def check_single_steps_of_a_large_field(spec, shape, stencil_march):
+def check_single_steps_of_a_large_field(spec, shape, stencil_march, storage="f32"):
     """A grid whose buffers pass the last cache (256 MB), by default plan: calls
     that leave one step, directly and in graphs, from both parities; then a
     Runge-Kutta model on the same grid, whose stage arguments the left-over
@@ -334,7 +334,7 @@ def check_single_steps_of_a_large_field(spec, shape, stencil_march):
     rk = W.ModelSpec(**dict(vars(spec), integrator="rk2"))
 
     def sequence(plan, chunk):
-        g = rd.Grid(shape, spec.ns, spec.h, "f32", stream=torch.cuda.Stream())
+        g = rd.Grid(shape, spec.ns, spec.h, storage, stream=torch.cuda.Stream())
         g.set_model(spec)
         g.set_plan(**dict(plan, graph_chunk=chunk))
         used = g.plan()
@@ -394,11 +394,11 @@ def test_march_tables_of_long_chunks(storage):
                         assert used["kernel"] == 8 and same(got, ref), (nz, model, name, plan)
 
 
-@pytest.mark.parametrize("model", ["diffusion", "turing"])
-def test_single_steps_of_a_large_19_point_field(model):
-    shape = {"diffusion": (300, 300, 384), "turing": (152, 300, 384)}[model]
+@pytest.mark.parametrize("model,storage", [("diffusion", "f32"), ("turing", "f32"), ("diffusion", "bf16")])
+def test_single_steps_of_a_large_19_point_field(model, storage):
+    shape = {"diffusion": (300, 300, 384) if storage == "f32" else (460, 300, 504), "turing": (152, 300, 384)}[model]
     spec = spec_of(model, shape, FACES["mirror"])
     spec.stencil = 19
     spec.K = [[max(k)] * 3 for k in spec.K]
-    assert 2 * spec.ns * 384 * shape[0] * shape[1] * 4 > 256 << 20
-    check_single_steps_of_a_large_field(spec, shape, True)
+    assert 2 * spec.ns * (-(-shape[2] // 64) * 64) * shape[0] * shape[1] * (4 if storage == "f32" else 2) > 256 << 20
+    check_single_steps_of_a_large_field(spec, shape, True, storage)
