@@ -502,16 +502,17 @@ double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m,
 }
 
 // The 19-point march.  Its plane takes longer where the fields come from memory:
-// with 0.9 us throughout (and 23 instructions for one field) long chunks of one
-// step a launch were predicted fastest for one large 16-bit field: diffusion BF16
-// 512^3 198 us a step, two steps a launch 106, 256x328x888 88 and 68; over 14
-// grids and all their plans the predicted best was 5.8 % off the measured on
-// average and up to 54 %, with these constants 3.1 and 17 %.
+// with 0.9 us throughout (and as many instructions for one field as within the
+// last cache) long chunks of one step a launch were predicted fastest for one
+// large 16-bit field: diffusion BF16 512^3 198 us a step, two steps a launch 106,
+// 256x328x888 88 and 62; over 14 grids and all their plans the predicted best
+// was 5.8 % off the measured on average and up to 54 %, with these constants 3.1
+// and 17 %.
 double march19_time(int storage, int pm, int k, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz, int cz) {
     const int nf = march19_fields(pm);
     const bool cached = 2.0 * nf * pitch_of(nx) * double(ny) * double(nz) * double(elem_size(storage)) <= double(kLastCache);
     MarchCost c{};
-    c.instr = (nf == 1 ? 20.0 : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
+    c.instr = (nf == 1 ? (cached ? 23.0 : 20.0) : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
     c.latency = cached ? 0.9 : 1.2, c.launch = 1.4, c.fill = 0.5;
     c.tbs = 5.96, c.halo_xy = 0.65, c.halo_z = 0.66;
     c.halo = k;
