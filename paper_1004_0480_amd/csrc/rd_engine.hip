@@ -798,6 +798,37 @@ bool march19_plan(const rd_grid* g, int steps, int lanes, rd_plan* out) {
     return best < 1e300;
 }
 
+// A grid of few rows on the march that `p` holds: its tiles, of whole lane rows,
+// store no more rows than they load as halos (few rows in the grid, or rows so
+// long that a workgroup holds few: ragged periodic ones have to stay whole), and
+// the slab is predicted to take less.  Both predictions are fits to some 1400
+// grids measured (the march's by its bias there); us a step of march and slab:
+// Brusselator, periodic, 725x300x200 274 and 192, 721x12896x2 288 and 91;
+// diffusion 351x3x985 9.6 and 8.5; pollutant 1024x2x1024 43 and 29, but
+// 498x10x2692 77 and 110, diffusion 411737x2x3 8.2 and 12.3.  With more rows the
+// march was never more than a tenth the slower.
+bool slab_for_few_rows(const rd_grid* g, const rd_plan& p) {
+    const StepArgs& a = g->args[0][0];
+    const MarchCfg c{p.ry, p.waves, p.prefetch};
+    const MarchGeom m = march_geom(a.nx, a.ny, a.bck[0][0] == BC_PERIODIC, c);
+    if (std::min<int64_t>(g->ny, m.by) > 2 * c.k + 1) return false;
+    const rd_plan sp = slab_plan(g);
+    if (sp.kernel != RD_KERNEL_BLOCK) return false;
+    auto whole = [](int64_t n, int64_t unit) { return double((n + unit - 1) / unit * unit); };
+    const double cells = whole(g->nx, 64 * sp.vx) * whole(g->ny, sp.ry * sp.waves) * whole(g->nz, sp.cz) * 1e-6;
+    if (cells < 1.0) return false;     // (launches of small grids are latency: the march's are fewer)
+    double march = 0.0, slab = 0.0;
+    for (int k = 0; k < g->npass; ++k) {
+        const int pm = g->pass_pm[k];
+        const bool one = march_fields(pm) == 1, poll = pm == PM_POLL1 || pm == PM_POLL2 || pm == PM_POLL2U;
+        march += march_time(g->storage, pm, c, m, g->nx, g->ny, g->nz, p.cz) / c.k *
+                 (poll ? 1.45 : one ? 1.1 : 0.85);
+        slab += one ? 5.0 + (poll ? 2.3 : 1.8) * cells * (g->storage == RD_F32 ? 1.0 : 0.87)
+                    : 7.0 + (poll ? 4.2 : 3.3) * cells * (g->storage == RD_F32 ? 1.0 : 0.87);
+    }
+    return march > slab;
+}
+
 // The default plan; *march: whether a register march takes the grid.
 rd_plan heuristic_plan(const rd_grid* g, bool* march = nullptr) {
     rd_plan best{};
@@ -815,6 +846,20 @@ rd_plan heuristic_plan(const rd_grid* g, bool* march = nullptr) {
     // 29 against 65; 64^3 8.4 against 26); its 19-point form against the ring or
     // direct plan chosen below (Turing FP32 192^3 20.8 and 44.5, 256^3 42.4 and
     // 67.8 (tuned ring 46.6), 130x101x77 8.5 and 59.6, 32^3 5.2 and 6.8)
+    if (takes && g->model != RD_MODEL_FRONT_CH && !g->args[0][0].s19 && slab_for_few_rows(g, best)) return slab_plan(g);
+    // A 19-point march of one row, or of hardly more over few planes, computes
+    // 14 or 30 rows of a tile for it, which pays on large sheets alone (us of the
+    // march and of the ring or direct plan, Turing: 1000003x1x1 176 and 44,
+    // 236x1x3036 42 and 27, 1000000x2x2 206 and 174; but 4096x1x4096 643 and 698,
+    // 1708x2x2166 154 and 341).
+    const bool sheet = g->ny > 1 || (g->nz >= 1024 && g->nx * g->nz >= (4LL << 20));
+    if (takes && g->args[0][0].s19 && (!sheet || g->ny * g->nz < 6)) {
+        rd_plan other{};
+        other.kernel = RD_KERNEL_DIRECT;
+        (void)ring_plan(g, &other);
+        int cfg = -1;
+        if (check_plan(g, other, &cfg) == RD_OK) return other;
+    }
     if (takes) return best;
     if (g->model == RD_MODEL_FRONT_CH && !g->args[0][0].s19) {
         // the one-pass front kernel, its largest shape for this storage

@@ -402,3 +402,24 @@ def test_single_steps_of_a_large_19_point_field(model, storage):
     spec.K = [[max(k)] * 3 for k in spec.K]
     assert 2 * spec.ns * (-(-shape[2] // 64) * 64) * shape[0] * shape[1] * (4 if storage == "f32" else 2) > 256 << 20
     check_single_steps_of_a_large_field(spec, shape, True, storage)
+
+
+def test_default_plans_of_few_rows():
+    """Grids on which a march's tiles hold few rows: long ragged periodic rows,
+    few rows of a large grid, a 19-point sheet of one row. The default is the
+    plan it was without a march, which a plan set by name may still take."""
+    cases = [("brusselator", 7, (20, 90, 725), "block", (1, 16, 2)), ("pollutant4", 7, (1024, 2, 1024), "block", (1, 8, 2)),
+             ("turing", 19, (256, 1, 256), "lds", None), ("diffusion", 19, (3, 1, 30000), "direct", None)]
+    for model, stencil, shape, kind, march in cases:
+        spec = spec_of(model, shape, FACES["periodic" if model == "brusselator" else "mirror"])
+        spec.stencil = stencil
+        if stencil == 19:
+            spec.K = [[max(k)] * 3 for k in spec.K]
+        f = fields_of(shape, spec.ns, 14)
+        ref, _ = run(spec, shape, f, "f32", [4], dict(kernel="direct"))
+        got, used = run(spec, shape, f, "f32", [4])
+        assert (used["kernel"], used["vx"] > 0 or kind == "direct") == (rd.KERNEL[kind], True) and same(got, ref), (model, shape, used)
+        if march:
+            ry, w, k = march
+            got, used = run(spec, shape, f, "f32", [4], dict(kernel="march", vx=4, ry=ry, waves=w, prefetch=k))
+            assert used["kernel"] == 8 and same(got, ref)
