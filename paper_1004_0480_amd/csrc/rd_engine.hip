@@ -2334,6 +2334,33 @@ int batch_march_tiles(const rd_grid* g) {
     return m.l == 0 ? 0 : int(m.tx * ((g->ny + m.by - 1) / m.by));
 }
 
+// Whether a tick of `run` steps marches: every member's grid has tiles, and the
+// march computes at most 3.3 times the cells, halos included, that the tiled
+// ring computes, which it does for half as many launches.  Rows that have to stay
+// whole (ragged periodic ones) leave it one row of five to store: us a step of
+// march and ring, 8 Brusselator grids of 64 x 64 rows in FP32: 325 cells (2.7
+// times) 50 and 68, 357 (5.3) 82 and 59, 405 (4.0) 85 and 62.  One step alone of
+// two FP32 fields beyond the last cache is bound by bytes and halves nothing: at
+// more than 1.25 times the ring takes it (2 grids of 256^3 (1.38) 174 and 153,
+// 384^3 (1.33) 263 and 246; 320^3 (1.17) 174 and 176, 2 of 224^3 (1.14) 117 and
+// 135).
+bool batch_marches(const std::vector<Member>& members, int64_t run) {
+    double march = 0.0, ring = 0.0, two = 0.0, all = 0.0;
+    for (const Member& m : members) {
+        if (m.march_tiles == 0) return false;
+        const rd_grid* g = m.g;
+        const double fields = g->model == RD_MODEL_BRUSSELATOR ? 2.0 : 1.0;
+        march += fields * g->nz * m.march_tiles * (64 * kBatchMarch.w * kMarchVX * kBatchMarch.ry);
+        ring += fields * g->nz * double((g->nx + kTrTile - 1) / kTrTile * kTrTile) *
+                double((g->ny + kBatchTr.by - 1) / kBatchTr.by * kBatchTr.by);
+        const double bytes = 2.0 * fields * double(g->plane) * g->nz * double(elem_size(g->storage));
+        all += bytes;
+        if (fields == 2.0 && g->storage == RD_F32) two += bytes;
+    }
+    const bool bytes_bound = run == 1 && all >= double(kLastCache) && two > 0.5 * all;
+    return march <= (bytes_bound ? 1.25 : 3.3) * ring;
+}
+
 // z planes per item of a tick: the fewest planes marched per workgroup slot,
 // plus half an item for the end of a launch, where the slots run dry one by
 // one.  An item marches four planes more than its chunk (the halo and the
@@ -2457,8 +2484,9 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
     }
     char* h_tab = b->h_tab2[tb];
     // Work list: every member's tiles, with its arguments for both parities,
-    // the grids with the largest tiles first (the kernel's workgroups claim
-    // items in list order, so the small ones fill in at the end of a step).
+    // the grids with the largest tiles first (workgroups claim a ring's items in
+    // list order, and a march's are dealt in it, so that the small ones fill in
+    // at the end of a step).
     const int ng = int(b->members.size());
     const size_t moff = meta_bytes(b->max_grids);
     int* meta = reinterpret_cast<int*>(h_tab);
@@ -2467,12 +2495,9 @@ extern "C" int rd_batch_step(rd_batch* b, int64_t chunk, rd_grid** finished, int
     long long items = 0;
     int64_t max_steps = 0;
     // two steps a launch where every member's grid allows, else one a launch
-    bool march = true;
-    for (const Member& m : b->members) {
-        max_steps = std::max(max_steps, m.steps_left);
-        march = march && m.march_tiles > 0;
-    }
+    for (const Member& m : b->members) max_steps = std::max(max_steps, m.steps_left);
     const int64_t run = std::min(chunk, max_steps);
+    const bool march = batch_marches(b->members, run);
     const int march_cz = march ? batch_march_chunk(b->members, b->march_blocks) : 0;
     std::vector<int> order(static_cast<size_t>(ng));
     for (int i = 0; i < ng; ++i) order[size_t(i)] = i;

@@ -423,3 +423,60 @@ def test_default_plans_of_few_rows():
             ry, w, k = march
             got, used = run(spec, shape, f, "f32", [4], dict(kernel="march", vx=4, ry=ry, waves=w, prefetch=k))
             assert used["kernel"] == 8 and same(got, ref)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_batches_that_return_to_the_ring(storage):
+    """Batches whose members' rows leave a march few rows to store, alone and
+    with others, even and odd ticks and single steps, between ticks that march:
+    the same bits as alone."""
+    import torch
+    ragged = ("brusselator", (6, 20, 389), "periodic", 7)
+    small = ("diffusion", (16, 32, 32), "mirror", 4)
+    for cases in ((ragged, ("brusselator", (5, 18, 405), "periodic", 3)), (ragged,) + (small,) * 5, (ragged, small)):
+        for chunk in (1, 3, 4):
+            stream = torch.cuda.Stream()
+            b = rd.Batch(8, 1 << 34, storage, stream=stream)
+            grids, refs = [], []
+            for i, (model, shape, faces, steps) in enumerate(cases):
+                spec = spec_of(model, shape, FACES[faces])
+                f = fields_of(shape, spec.ns, steps + i)
+                refs.append(run(spec, shape, f, storage, [steps], dict(kernel="direct"))[0])
+                g = rd.Grid(shape, spec.ns, spec.h, storage, stream=stream)
+                g.set_model(spec)
+                for s, x in enumerate(f):
+                    g.write(s, x)
+                b.add(g, steps)
+                grids.append(g)
+            done = []
+            while len(done) < len(grids):
+                done += b.step(chunk)
+            for g, ref in zip(grids, refs):
+                assert same(g.read_all(np.float32), ref), (g.shape, chunk)
+            b.close()
+            for g in grids:
+                g.close()
+
+
+def test_single_steps_of_a_large_batch():
+    """A batch of two FP32 fields beyond the last cache, stepped one step and
+    three steps a tick: both forms of the launch, from either parity."""
+    import torch
+    shape = (256, 256, 258)
+    spec = spec_of("brusselator", shape, FACES["mirror"])
+    rng = np.random.default_rng(3)
+    f = [rng.random(shape, dtype=np.float32) + np.float32(0.5) for _ in range(2)]
+    ref = [x[::5] for x in run(spec, shape, f, "f32", [6], dict(kernel="direct"))[0]]
+    for ticks in ((1,) * 6, (3, 1, 1, 1), (1, 3, 2)):
+        stream = torch.cuda.Stream()
+        b = rd.Batch(1, 1 << 34, "f32", stream=stream)
+        g = rd.Grid(shape, 2, spec.h, "f32", stream=stream)
+        g.set_model(spec)
+        for s, x in enumerate(f):
+            g.write(s, x)
+        b.add(g, 6)
+        done = [b.step(n) for n in ticks][-1]
+        assert len(done) == 1
+        assert same([x[::5] for x in g.read_all(np.float32)], ref), ticks
+        b.close()
+        g.close()
