@@ -366,22 +366,44 @@ void fill_mirror(StepArgs& a, int f) {
 // that takes the fewest workgroups (one tile: whole rows; more: a halo lane on
 // each side, which needs rows of whole lanes on a periodic axis).  l = 0: none.
 struct MarchGeom { int l, halo, tx, by, by1; };
-MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c) {
+
+// What the edges of x tiles cost in bytes, as a share of one read of the fields:
+// lines that a tile reads for a halo lane or shares with the next tile come from
+// the caches in part (0.25), those that two tiles write in part reach memory as
+// more (0.8; half of that where tiles meet at half lines).  `line` cells a line.
+double tile_edges(const MarchGeom& m, int nx, int line) {
+    const int stored = (m.l - 2 * m.halo) * kMarchVX, lanes = line / kMarchVX;
+    if (!line || !m.halo) return 0.0;
+    const bool whole = stored % line == 0;
+    const double read = whole ? stored / line + 2.0 : double(m.l) / lanes + 1.0 - 1.0 / lanes;
+    const double shared = whole ? 0.0 : stored % (line / 2) == 0 ? 0.5 : 1.0;
+    return 0.25 * (read * m.tx * line / nx - 1.0) + 0.8 * shared * m.tx * line / nx;
+}
+
+// `line`: cells of a memory line where the tiles' edges are to count (tiles of
+// whole lines are tried then too), else 0.
+MarchGeom march_geom(int nx, int ny, bool periodic_x, const MarchCfg& c, int line = 0) {
     MarchGeom best{};
     const int nx4 = (nx + kMarchVX - 1) / kMarchVX, t = 64 * c.w;
-    long long best_n = 0;
+    double best_n = 0.0;
+    auto consider = [&](int l, int halo) {
+        if (l > t) return;
+        const int rows = t / l * c.ry, by = rows - 2 * c.k;
+        if (by < 1) return;
+        const MarchGeom m{l, halo, (nx4 + l - 2 * halo - 1) / (l - 2 * halo), by, rows - 2};
+        const double n = double(m.tx) * ((ny + by - 1) / by) * (1.0 + 0.5 * tile_edges(m, nx, line));
+        if (best.l == 0 || n < best_n) {
+            best = m;
+            best_n = n;
+        }
+    };
     for (int tx = 1; tx <= nx4 && tx <= 4096; ++tx) {
         // (rows of fewer lanes leave the rest of a tile's least idle)
         const int halo = tx > 1 ? 1 : 0, l = tx > 1 ? (nx4 + tx - 1) / tx + 2 : std::max(nx4, kMarchMinLanes);
         if (l > t) continue;
         if (l < kMarchMinLanes || (halo && periodic_x && nx % kMarchVX != 0)) break;
-        const int rows = t / l * c.ry, by = rows - 2 * c.k;
-        if (by < 1) continue;
-        const long long n = (long long)((nx4 + l - 2 * halo - 1) / (l - 2 * halo)) * ((ny + by - 1) / by);
-        if (best.l == 0 || n < best_n) {
-            best = MarchGeom{l, halo, (nx4 + l - 2 * halo - 1) / (l - 2 * halo), by, rows - 2};
-            best_n = n;
-        }
+        consider(l, halo);
+        if (line && halo) consider((l - 2 + line / kMarchVX - 1) / (line / kMarchVX) * (line / kMarchVX) + 2, halo);
     }
     return best;
 }
@@ -421,6 +443,18 @@ MarchGeom march19_geom(int nx, bool periodic_x, int k, int ry) {
 
 constexpr int kFrontHalo = 2;   // rows a tile of the front kernel loses on each side
 
+// Its lane geometry.  FP32 fields beyond the last cache are bound by their bytes,
+// in whole lines of memory: tiles by their count alone took 771x318x362 817 us a
+// step (15 tiles of 52 cells a row), these 484 (5 of 160), 1021x300x200 431 and
+// 316, 725x300x200 309 and 254, where the LDS form takes 604, 426 and 246.
+// (16-bit fields and smaller ones gained on some grids what they lost on others.)
+int front_line(int64_t nx, int64_t ny, int64_t nz, int storage) {
+    return storage == RD_F32 && 6.0 * 4.0 * pitch_of(nx) * double(ny) * double(nz) > double(kLastCache) ? 32 : 0;
+}
+MarchGeom front_geom(int64_t nx, int64_t ny, int64_t nz, int storage, const FmarchCfg& c) {
+    return march_geom(int(nx), int(ny), false, {c.ry, c.w, kFrontHalo}, front_line(nx, ny, nz, storage));
+}
+
 // The faces the register-march front kernel takes: mirror for C, and along x
 // and y for A and B, whose z faces may also be held or fixed ghosts.
 bool fmarch_axes(const StepArgs& a) {
@@ -441,6 +475,7 @@ struct MarchCost {
     double fill;              // planes the start of a march costs
     double tbs;               // TB/s of the bytes
     double halo_xy, halo_z;   // share of the halo reads that reach memory
+    double writes;            // bytes written, of the fields'
     int halo;                 // rows and planes a tile needs on each side
     int extra;                // planes a march computes beyond its chunk
     double cell_bytes;        // of the fields, read (and as many written)
@@ -458,7 +493,7 @@ double march_cost(const MarchCost& k, int ry, int w, const MarchGeom& m, int64_t
     if (rest) us += planes * std::max(k.latency, double((rest + cus - 1) / cus) * issue);
     const double over = double(m.l) / (m.l - 2 * m.halo) * (m.by + 2 * k.halo) / m.by - 1.0;
     const double reads = (1.0 + k.halo_xy * over) * (1.0 + k.halo_z * (k.halo + k.extra) / cz);
-    const double mem = double(nx) * ny * nz * k.cell_bytes * (1.0 + reads) / (k.tbs * 1e6);
+    const double mem = double(nx) * ny * nz * k.cell_bytes * (k.writes + reads) / (k.tbs * 1e6);
     return std::pow(std::pow(us, 4.0) + std::pow(mem, 4.0), 0.25) + k.launch;
 }
 
@@ -475,7 +510,7 @@ double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, in
     k.instr = (nf == 1 ? (poll ? 19.0 : 12.0) : poll ? 41.0 : 38.6) * (storage == ST_F32 ? 1.0 : 1.12) * c.k;
     if (poll && nf == 2 && storage == ST_F32 && c.w == 16) k.instr *= 1.35;   // spills at 128 registers
     k.latency = 0.81, k.launch = 1.36, k.fill = 1.95;
-    k.tbs = 5.96, k.halo_xy = 0.65, k.halo_z = 0.66;
+    k.tbs = 5.96, k.halo_xy = 0.65, k.halo_z = 0.66, k.writes = 1.0;
     k.halo = c.k;
     k.extra = 2 * (c.k - 1);
     k.cell_bytes = nf * double(elem_size(storage));
@@ -485,14 +520,19 @@ double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, in
 }
 
 // The front kernel: a fit to 14 grids from 64^3 to 384x384x512 (FP32 and BF16),
-// 11 % off on average, its plans within 3 % of the best measured.
+// 11 % off on average, its plans within 3 % of the best measured; of FP32 beyond
+// the last cache to 446 plans of 70 grids, 13 % off (22 without the tiles' edges).
 double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz,
                    int cz) {
     const int t = 64 * c.w;
     MarchCost k{};
     k.instr = 70.7 * (storage == ST_F32 ? 1.0 : 1.035) * (sr ? 1.6 : 1.0);   // (the generator's calls)
     k.latency = 1.22, k.launch = 1.02, k.fill = 1.38;
-    k.tbs = 5.09, k.halo_xy = 0.33, k.halo_z = 1.1;
+    k.tbs = 5.09, k.halo_xy = 0.33, k.halo_z = 1.1, k.writes = 1.0;
+    if (const int line = front_line(nx, ny, nz, storage)) {
+        k.tbs = 4.3, k.halo_xy = 0.0, k.halo_z = 0.3;
+        k.writes = 1.0 + tile_edges(m, int(nx), line);
+    }
     k.halo = kFrontHalo;
     k.extra = 2;
     k.cell_bytes = 3 * double(elem_size(storage));
@@ -514,7 +554,7 @@ double march19_time(int storage, int pm, int k, const MarchGeom& m, int64_t nx, 
     MarchCost c{};
     c.instr = (nf == 1 ? (cached ? 23.0 : 20.0) : 50.0) * k * (storage == ST_F32 ? 1.0 : 1.12);
     c.latency = cached ? 0.9 : 1.2, c.launch = 1.4, c.fill = 0.5;
-    c.tbs = 5.96, c.halo_xy = 0.65, c.halo_z = 0.66;
+    c.tbs = 5.96, c.halo_xy = 0.65, c.halo_z = 0.66, c.writes = 1.0;
     c.halo = k;
     c.extra = 3 * k - 1;
     c.cell_bytes = nf * double(elem_size(storage));
@@ -550,7 +590,8 @@ long long set_tiling(StepArgs& a, const rd_plan& p, int storage = ST_F32, int pm
     if (is_march(p)) {
         const bool per = a.bck[0][0] == BC_PERIODIC;
         const MarchGeom g = s19 ? march19_geom(a.nx, per, p.prefetch, p.ry)
-                                : march_geom(a.nx, a.ny, per, {p.ry, p.waves, front ? kFrontHalo : p.prefetch});
+                          : front ? front_geom(a.nx, a.ny, a.nz, storage, {p.ry, p.waves})
+                                : march_geom(a.nx, a.ny, per, {p.ry, p.waves, p.prefetch});
         a.mg[MG_LANES] = g.l;
         a.mg[MG_HALO] = g.halo;
         a.mg[MG_STEPS] = p.prefetch;
@@ -654,7 +695,7 @@ bool fmarch_plan(const rd_grid* g, int shape, rd_plan* out) {
         int cfg = -1;
         if (check_plan(g, p, &cfg) != RD_OK) continue;
         const StepArgs& a = g->args[0][1];
-        const MarchGeom m = march_geom(a.nx, a.ny, false, {c.ry, c.w, kFrontHalo});
+        const MarchGeom m = front_geom(g->nx, g->ny, g->nz, g->storage, c);
         for (int n = 1; n <= 64 && n <= g->nz; ++n) {
             p.cz = int((g->nz + n - 1) / n);
             const double us = fmarch_time(g->storage, a.sr != 0, c, m, g->nx, g->ny, g->nz, p.cz);
@@ -964,7 +1005,7 @@ int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out) {
         if (!fmarch_axes(a) || a.kx[2] != 0.f || a.ky[2] != 0.f || a.kz[2] != 0.f)
             return fail(RD_EINVAL, "the register-march front plan takes mirror faces (A and B also held or ghost "
                                    "z faces) and a C without a Fickian term");
-        if (march_geom(a.nx, a.ny, false, {p.ry, p.waves, kFrontHalo}).l == 0)
+        if (front_geom(g->nx, g->ny, g->nz, g->storage, {p.ry, p.waves}).l == 0)
             return fail(RD_EINVAL, "the register march has no tile for this grid");
         *cfg_out = cfg;
         return RD_OK;
@@ -2133,7 +2174,7 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
     for (int i = 0; i < kNumFmarchCfgs && !g->args[0][0].s19 && g->model == RD_MODEL_FRONT_CH; ++i) {
         rd_plan p{};
         if (!fmarch_plan(g, i, &p)) continue;
-        const MarchGeom m = march_geom(int(g->nx), int(g->ny), false, {p.ry, p.waves, kFrontHalo});
+        const MarchGeom m = front_geom(g->nx, g->ny, g->nz, g->storage, {p.ry, p.waves});
         for (int cz : march_chunks(g, m, p.cz)) {
             p.cz = cz;
             cands.push_back(p);
