@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstddef>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <string>
@@ -494,7 +495,7 @@ double march_cost(const MarchCost& k, int ry, int w, const MarchGeom& m, int64_t
     const double over = double(m.l) / (m.l - 2 * m.halo) * (m.by + 2 * k.halo) / m.by - 1.0;
     const double reads = (1.0 + k.halo_xy * over) * (1.0 + k.halo_z * (k.halo + k.extra) / cz);
     const double mem = double(nx) * ny * nz * k.cell_bytes * (k.writes + reads) / (k.tbs * 1e6);
-    return std::pow(std::pow(us, 4.0) + std::pow(mem, 4.0), 0.25) + k.launch;
+    return std::sqrt(std::sqrt(us * us * us * us + mem * mem * mem * mem)) + k.launch;
 }
 
 // The constants are a fit to 27 grids from 64^3 to 512^3 with every shape and 5
@@ -1118,7 +1119,9 @@ int apply_plan(rd_grid* g, bool named = false) {
             if (p.kernel == RD_KERNEL_TILED || p.kernel == RD_KERNEL_BLOCK || p.kernel == RD_KERNEL_LDS ||
                 p.kernel == RD_KERNEL_LDS2 || p.kernel == RD_KERNEL_FUSED || p.kernel == RD_KERNEL_TRING ||
                 p.kernel == RD_KERNEL_MARCH) {
-                g->blocks[k] = set_tiling(a, p, g->storage, g->pass_pm[k]);
+                // (both parities are tiled alike: one search for the single steps' chunks)
+                g->blocks[k] = set_tiling(a, p, g->storage, par == 0 ? g->pass_pm[k] : -1);
+                if (par == 1) std::copy(std::begin(g->args[0][k].mg), std::end(g->args[0][k].mg), std::begin(a.mg));
                 if (p.kernel == RD_KERNEL_MARCH) {
                     const bool per = a.bck[0][0] == BC_PERIODIC;
                     const MarchGeom mg = march_geom(a.nx, a.ny, per, kMarchCfgs[cfg]);
