@@ -2273,8 +2273,9 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
         g->cur = cur0;
         return ms * 1e3f / float(n);
     };
-    // every candidate once; then the four fastest twice more, over twice the
-    // steps and in turn, so that near ties are settled by the longer runs
+    // every candidate once; then the four fastest, and the four fastest that are
+    // no march, twice more, over twice the steps and in turn, so that near ties
+    // are settled by the longer runs
     std::vector<std::pair<float, rd_plan>> timed;
     for (const rd_plan& p : cands) {
         const float us = time_plan(p, trial_steps);
@@ -2286,23 +2287,25 @@ extern "C" int rd_autotune(rd_grid* g, int32_t trial_steps, rd_plan* best) {
                          [](const std::pair<float, rd_plan>& x, const std::pair<float, rd_plan>& y) {
                              return x.first < y.first;
                          });
-        const size_t top = std::min<size_t>(4, timed.size());
-        std::vector<float> acc(top, 0.f);
+        std::vector<size_t> again;
+        size_t others = 0;
+        for (size_t i = 0; i < timed.size(); ++i) {
+            const bool other = !is_march(timed[i].second);
+            if (again.size() < 4 || (other && others < 4)) again.push_back(i);
+            others += other;
+        }
+        std::vector<float> acc(again.size(), 0.f);
         for (int rep = 0; rep < 2 && rc == RD_OK; ++rep)
-            for (size_t i = 0; i < top && rc == RD_OK; ++i) {
-                const float us = time_plan(timed[i].second, 2 * trial_steps);
+            for (size_t i = 0; i < again.size() && rc == RD_OK; ++i) {
+                const float us = time_plan(timed[again[i]].second, 2 * trial_steps);
                 acc[i] += us >= 0.f ? us : 1e30f;
             }
-        size_t bi = 0;
-        for (size_t i = 1; i < top; ++i)
-            if (acc[i] < acc[bi]) bi = i;
-        if (rc == RD_OK) best_plan = timed[bi].second;
-        // (of the plans that are no march, the longer runs decide between those
-        // among the four)
-        size_t gi = timed.size();
-        for (size_t i = timed.size(); i-- > 0;)
-            if (!is_march(timed[i].second) && (i >= top || gi >= top || acc[i] < acc[gi])) gi = i;
-        if (gi < timed.size()) general = timed[gi].second;
+        float bus = 2e30f, gus = 2e30f;
+        for (size_t i = 0; i < again.size() && rc == RD_OK; ++i) {
+            const rd_plan& p = timed[again[i]].second;
+            if (acc[i] < bus) bus = acc[i], best_plan = p;
+            if (!is_march(p) && acc[i] < gus) gus = acc[i], general = p;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
