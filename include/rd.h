@@ -368,8 +368,10 @@ int rd_set_rounding(rd_grid *g, int32_t mode, uint64_t seed);
  * per-process cache keyed by shape, species, model, storage and whether a
  * register march takes the grid (its faces and rounding), and return it in
  * *best; the fastest plan of the other kinds is kept for grids that no march
- * takes, until one of them is tuned.  The grid's state is saved before and restored after, so the call
- * leaves the fields as they were.  Synchronous. */
+ * takes, until one of them is tuned.  (A ring found so serves no such grid that
+ * it would slow down: 7-point fields with held or ghost faces.)  The grid's
+ * state is saved before and restored after, so the call leaves the fields as
+ * they were.  Synchronous. */
 int rd_autotune(rd_grid *g, int32_t trial_steps, rd_plan *best);
 
 /* ---------------------------------------------------------- batched form */

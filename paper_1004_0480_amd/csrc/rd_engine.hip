@@ -1085,6 +1085,23 @@ bool one_pass(const rd_grid* g) {
     return g->eff.kernel == RD_KERNEL_FUSED;
 }
 
+// Whether a plan that was tuned on a grid which a march takes serves this one,
+// which none takes.  7-point rings form held and ghost values at every cell, and
+// the tiled one draws for every level: there they lose to the default (us a step:
+// held x face, pollutant 250^3 ring 554, default 173, Brusselator 192^3 74 and
+// 48; 16-bit with rounding, pollutant 725x101x100 116 and 96).  The other plans
+// and the other forms carry over (Turing, 19-point, 192^3 70 and 106; Brusselator
+// 512x512x128 with rounding 118 and 146).
+bool inherits(const rd_grid* g, const rd_plan& p) {
+    if (p.kernel == RD_KERNEL_TRING) return false;
+    if (g->model == RD_MODEL_FRONT_CH || g->args[0][0].s19 ||
+        (p.kernel != RD_KERNEL_LDS && p.kernel != RD_KERNEL_LDS2))
+        return true;
+    for (int k = 0; k < g->npass; ++k)
+        if (!march_axes(g->args[0][k], march_fields(g->pass_pm[k]))) return false;
+    return true;
+}
+
 // Resolve the plan in use, fill tiling into the argument copies, upload them.
 // A register-march plan takes fewer integrators, roundings and faces than the
 // plans that autotuning found before it: `named` (rd_set_plan) refuses one that
@@ -1100,8 +1117,9 @@ int apply_plan(rd_grid* g, bool named = false) {
         const rd_plan h = heuristic_plan(g, &march);
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);
-            const rd_plan* tuned = g_tune_cache.get(tune_key(g), march);
-            p = tuned ? *tuned : h;
+            bool own = false;
+            const rd_plan* tuned = g_tune_cache.get(tune_key(g), march, &own);
+            p = tuned && (own || inherits(g, *tuned)) ? *tuned : h;
         }
         p.graph_chunk = gc;
         // a cached plan this grid cannot take (other settings since it was

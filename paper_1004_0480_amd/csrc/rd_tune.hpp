@@ -14,10 +14,10 @@ namespace rdk {
 // storage), for two classes of grids: those a register march takes and those
 // it does not, for their faces or rounding.  A march is mostly the fastest
 // plan of the former and none of the latter, so neither class answers for the
-// other: held faces would lose a tuned ring to a march that refuses them, and
-// mirror ones would be kept on a ring by a grid with held faces.  What was
-// timed of the other plans on a march's grid serves the latter until one of
-// them is tuned itself.
+// other: held faces would lose their own plan to a march that refuses them, and
+// mirror ones would be kept on a ring by a grid with held faces.  What was timed
+// of the other plans on a march's grid is kept for the latter until one of them
+// is tuned itself.
 class PlanCache {
 public:
     using Key = std::tuple<int64_t, int64_t, int64_t, int, int, int>;
@@ -31,13 +31,17 @@ public:
             general_[k] = {best, true};
         }
     }
-    const rd_plan* get(const Key& k, bool march_grid) const {
+    // *own: tuned on a grid of that class itself.
+    const rd_plan* get(const Key& k, bool march_grid, bool* own) const {
+        *own = true;
         if (march_grid) {
             const auto it = march_.find(k);
             return it == march_.end() ? nullptr : &it->second;
         }
         const auto it = general_.find(k);
-        return it == general_.end() ? nullptr : &it->second.plan;
+        if (it == general_.end()) return nullptr;
+        *own = it->second.tuned;
+        return &it->second.plan;
     }
 
 private:

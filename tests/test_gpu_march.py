@@ -299,6 +299,25 @@ def test_tuning_one_class_of_faces_leaves_the_other_its_plans():
             assert used["mirror"]["kernel"] == 8
 
 
+def test_held_faces_borrow_no_ring():
+    """A 7-point ring that was timed on a grid with mirror faces is not lent to
+    one with held faces, where it is slower than the default plan."""
+    mirror = FACES["mirror"]
+    for model, shape, storage in (("brusselator", (192, 192, 192), "f32"), ("pollutant4", (100, 101, 725), "bf16")):
+        plans = []
+        for faces in (mirror, (HELD,) + mirror[1:]):
+            spec = spec_of(model, shape, faces)
+            g = rd.Grid(shape, spec.ns, 1.0, storage)
+            g.set_model(spec)
+            for s in range(spec.ns):
+                g.write(s, np.full(shape, 0.5, np.float32))
+            if faces is mirror:
+                g.autotune(4)
+            plans.append(g.plan()["kernel"])
+            g.close()
+        assert plans[1] not in (4, 5, 7), (model, plans)
+
+
 def test_march19_orders_bitwise():
     """Both tile orders of the 19-point march, with left-over launches, on grids
     of several tiles along every axis."""

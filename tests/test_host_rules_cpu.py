@@ -88,8 +88,9 @@ extern "C" void put(int n, int march, int best, int general) {
     cache.put(key(n), march != 0, b, general ? &g : nullptr);
 }
 extern "C" int get(int n, int march) {
-    const rd_plan* p = cache.get(key(n), march != 0);
-    return p ? p->kernel : 0;
+    bool own;
+    const rd_plan* p = cache.get(key(n), march != 0, &own);
+    return p ? (own ? 1 : -1) * p->kernel : 0;
 }
 """)
     return lib
@@ -112,14 +113,14 @@ def test_tuned_plans_serve_their_own_class_of_grids(tune):
     tune.put(1, 0, ring, ring)                 # a grid with held faces, tuned alone
     assert tune.get(1, 0) == ring and tune.get(1, 1) == 0
     tune.put(2, 1, march, ring)                # a march's grid: its best other plan serves the rest
-    assert tune.get(2, 1) == march and tune.get(2, 0) == ring
+    assert tune.get(2, 1) == march and tune.get(2, 0) == -ring        # (negative: not tuned on its own class)
     tune.put(2, 0, tring, tring)               # which are then tuned themselves, and keep that
     tune.put(2, 1, lds, lds)                   # (another plan may beat the march on its own grid)
     assert tune.get(2, 0) == tring and tune.get(2, 1) == lds
     tune.put(3, 1, march, 0)                   # none but marches ran
     assert tune.get(3, 0) == 0 and tune.get(4, 0) == tune.get(4, 1) == 0
     tune.put(3, 1, march, ring)
-    assert tune.get(3, 0) == ring
+    assert tune.get(3, 0) == -ring
 
 
 # ------------------------------------------------------------ tiles of a march
