@@ -166,11 +166,13 @@ enum {
     RD_KERNEL_AUTO = 0,    /* library choice: the rd_autotune cache entry for
                               this shape, model and integrator, else a heuristic:
                               a register march where one takes the grid (MARCH,
-                              FUSED or LDS with vx 0), else the one-pass plan for
-                              the 7-point front model, a slab shape for other
-                              7-point models, and for 19-point ones the first
-                              LDS-ring shape, with z chunks for about two
-                              workgroups per CU.  A register-march plan that was
+                              FUSED or LDS with vx 0) and, for other models than
+                              the front's, its rows are not so few that the march
+                              would compute more halo than grid; else the one-pass
+                              plan for the 7-point front model, a slab shape for
+                              other 7-point models, and for 19-point ones the
+                              first LDS-ring shape, with z chunks for about two
+                              workgroups per CU, or DIRECT.  A register-march plan that was
                               set by name gives way to this choice while the
                               model or rounding is one it does not take         */
     RD_KERNEL_DIRECT = 1,  /* one thread per cell, neighbours through the cache */
@@ -379,9 +381,10 @@ int rd_autotune(rd_grid *g, int32_t trial_steps, rd_plan *best);
 /* A batch steps many grids of uneven size together: each launch is one
  * persistent kernel that walks a work list of (grid, tile) items covering
  * every active grid (two steps of each where every grid is one that
- * RD_KERNEL_MARCH takes), and rd_batch_step replays a captured hipGraph of such
- * launches.  Grids must use the DIFFUSION or BRUSSELATOR model, share the
- * batch's storage dtype and stay alive while in the batch.
+ * RD_KERNEL_MARCH takes and few of its cells are computed in vain), and
+ * rd_batch_step replays a captured hipGraph of such launches.  Grids must use
+ * the DIFFUSION or BRUSSELATOR model, share the batch's storage dtype and stay
+ * alive while in the batch.
  * hbm_budget_bytes caps the summed rd_grid_bytes of member grids. */
 int rd_batch_create(int32_t max_grids, size_t hbm_budget_bytes, int32_t storage_dtype,
                     void *hip_stream, rd_batch **out);

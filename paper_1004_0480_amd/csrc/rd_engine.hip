@@ -44,10 +44,11 @@ int fail(int code, const std::string& msg) {
     } while (0)
 
 // Field buffers start at different places of the memory's interleave (17 units
-// of 256 bytes apart), so that the streams of a step, which run through all
-// fields at the same cells, do not meet in the same channels (front 384x384x512
-// FP32, six streams: 391 us a step with buffers at equal offsets, 374 so; with
-// 64 KB, 1 MB or 2 MB more between them the same).
+// of 256 bytes apart), since the streams of a step run through all fields at the
+// same cells, and at equal offsets may meet in the same channels (no counter was
+// read for that; the time shows it: front 384x384x512 FP32, six streams, 391 us a
+// step with buffers at equal offsets, 374 so; with 64 KB, 1 MB or 2 MB more
+// between them the same).
 constexpr size_t kStagger = 17 * 256;
 size_t stagger_bytes(int buffer) { return size_t(buffer) * kStagger; }
 
@@ -500,8 +501,8 @@ double march_cost(const MarchCost& k, int ry, int w, const MarchGeom& m, int64_t
 
 // The constants are a fit to 27 grids from 64^3 to 512^3 with every shape and 5
 // to 14 chunk lengths each (diffusion, Brusselator, pollutant; FP32 and BF16):
-// 12 % off on average, and the plans of least predicted time within 4 % of the
-// best measured.  (The pollutant's instructions are counted, and checked on
+// 12 % off on average, and the plans of least predicted time mostly within 4 % of
+// the best measured (diffusion BF16 512^3 79 and 72 us a step is the most known).  (The pollutant's instructions are counted, and checked on
 // eleven grids: the predicted plans were within 10 % of the autotuned.)
 double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz,
                   int cz) {
@@ -521,8 +522,9 @@ double march_time(int storage, int pm, const MarchCfg& c, const MarchGeom& m, in
 }
 
 // The front kernel: a fit to 14 grids from 64^3 to 384x384x512 (FP32 and BF16),
-// 11 % off on average, its plans within 3 % of the best measured; of FP32 beyond
-// the last cache to 446 plans of 70 grids, 13 % off (22 without the tiles' edges).
+// 11 % off on average, its plans mostly within 3 % of the best measured (BF16
+// 384x384x512 254 and 232 us a step, 248x200x180 32 and 29); of FP32 beyond the
+// last cache to 446 plans of 70 grids, 13 % off (22 without the tiles' edges).
 double fmarch_time(int storage, bool sr, const FmarchCfg& c, const MarchGeom& m, int64_t nx, int64_t ny, int64_t nz,
                    int cz) {
     const int t = 64 * c.w;
@@ -639,9 +641,6 @@ bool ring_row_fits(const rd_grid* g, int nch) {
     return g->nx <= 256 * nch && g->nx > 256 * (nch - 1) && g->nx % (g->storage == RD_F32 ? 4 : 8) == 0;
 }
 
-// Default plan: the plane-block kernel with the compiled slab shape that
-// wastes the fewest lanes and rows (ties: wider rows, one row per wave,
-// four-plane slabs, multi-wave workgroups).
 int check_plan(const rd_grid* g, const rd_plan& p, int* cfg_out);
 
 // z chunk length of a ring plan with `tiles` xy tiles and one workgroup per
@@ -682,7 +681,8 @@ int balanced_cz_k(const rd_grid* g, long long tiles, int k) {
     return best;
 }
 
-// The same for the front kernel.
+// The register-march front plan (shape -1: any) of least predicted time; false
+// if no shape takes the grid.
 bool fmarch_plan(const rd_grid* g, int shape, rd_plan* out) {
     double best = 1e300;
     for (int i = 0; i < kNumFmarchCfgs; ++i) {
@@ -721,7 +721,8 @@ std::vector<int> march_chunks(const rd_grid* g, const MarchGeom& m, int predicte
     return czs;
 }
 
-// The slab shape that wastes the fewest lanes and rows.
+// The compiled slab shape that wastes the fewest lanes and rows (ties: wider
+// rows, one row per wave, four-plane slabs, multi-wave workgroups).
 rd_plan slab_plan(const rd_grid* g) {
     rd_plan best{};
     best.kernel = RD_KERNEL_DIRECT;
@@ -879,15 +880,17 @@ rd_plan heuristic_plan(const rd_grid* g, bool* march = nullptr) {
                        : g->args[0][0].s19           ? march19_plan(g, 0, 0, &best)
                                                      : march_plan(g, -1, &best);
     if (march) *march = takes;
-    // The register march wherever it applies: on every grid measured it beat
-    // the slab this rule chose before, and the best of the other plans
-    // (us per step, FP32: diffusion 512^3 77 against 189, Brusselator 256^3 28
-    // against 44, pollutant 512x512x128 131 against 218, diffusion 64^3 2.5
-    // against 6.1); its front form against the one-pass LDS form (384x384x512
-    // FP32 376 against 420, BF16 232 against 383; 248x200x180 42 against 62 and
-    // 29 against 65; 64^3 8.4 against 26); its 19-point form against the ring or
-    // direct plan chosen below (Turing FP32 192^3 20.8 and 44.5, 256^3 42.4 and
-    // 67.8 (tuned ring 46.6), 130x101x77 8.5 and 59.6, 32^3 5.2 and 6.8)
+    // The register march wherever it applies, but for grids of few rows: it beats
+    // the slab this rule chose before, and the best of the other plans when tuned
+    // (us per step, FP32, march, slab, tuned: diffusion 512^3 79, 209 and 189,
+    // Brusselator 256^3 28.5, 60 and 44, pollutant 512x512x128 124, 301 and 218,
+    // diffusion 64^3 2.2, 6.2 and 6.1); its front form the one-pass LDS form
+    // (384x384x512 FP32 371 and 427, BF16 254 and 381; 248x200x180 42 and 62, 32
+    // and 65; 64^3 7.3 and 26); its 19-point form the ring or direct plan chosen
+    // below (Turing FP32 192^3 20.7 and 43.8, 256^3 42.2 and 67.8 (tuned ring
+    // 46.6), 130x101x77 8.4 and 59.6, 32^3 5.4 and 6.9).  Over some 5000 grids
+    // and calls of all kinds what is left slower than that rule is at most 15 %
+    // so (thin odd grids: Brusselator 399x5x1876, pollutant 1697x4x255).
     if (takes && g->model != RD_MODEL_FRONT_CH && !g->args[0][0].s19 && slab_for_few_rows(g, best)) return slab_plan(g);
     // A 19-point march of one row, or of hardly more over few planes, computes
     // 14 or 30 rows of a tile for it, which pays on large sheets alone (us of the

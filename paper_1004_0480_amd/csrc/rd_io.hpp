@@ -11,8 +11,8 @@ namespace rdk {
 // Fields are walked as rows (padded rows start every `pitch` cells, dense ones
 // every nx) of units of four cells, the last of a row holding what is left.
 // A workgroup owns a run of whole rows (or a part of a long one) and its threads
-// take the run's units in turn, several at a time (DEPTH) so that several loads of a thread are in
-// flight, or one where a thread has no more than one anyway:
+// take the run's units in turn, several at a time (DEPTH) so that several loads
+// of a thread are in flight, or one where a thread has no more than one anyway:
 // one 32-bit division per unit finds its row, where a division in 64 bits per
 // cell would cost more than the cell's bytes.  Bound by memory: 403x301x300 FP32
 // (146 MB a field, fastest traced, cell by cell before against this) write
@@ -29,7 +29,7 @@ __device__ __forceinline__ IoUnit io_unit(unsigned u, unsigned units, int nx4, i
 // The four cells from `at` on of `end` readable ones, moved back where they
 // would pass the end (io_cells puts that right), so that the loads of a turn
 // are one straight run (a branch around each, for the units at the ends of rows:
-// reduction 43 us, read 57).  The address need only be aligned to a cell
+// reduction 41 us, read 57).  The address need only be aligned to a cell
 // (dense rows start anywhere).
 template <class T>
 __device__ __forceinline__ Vec<T, 4> io_load(const void* base, long long at, long long end) {

@@ -37,20 +37,25 @@
 // them would; every cell goes through the model's own cell function, so K steps
 // give the bits of K launches of one.
 //
-// Measured (us per step, default plans; one step per launch, the best plan
-// before, against this): diffusion 512^3 FP32 189 -> 77 (K 4: 1740 Gcell/s, 2.2
-// times what the bytes of single steps would allow at 8 TB/s), BF16 121 -> 68;
-// Brusselator 256^3 FP32 44.3 -> 28.0, BF16 42.3 -> 28.2; pollutant 512x512x128
-// FP32 218 -> 131; small grids, where a launch is the latency of its chain of
-// loads: diffusion 64^3 6.1 -> 2.5, Brusselator 101x90x77 10.2 -> 4.9.  At
-// diffusion 512^3, K 2, the vector units were busy 59 % of the time and 5.3 TB/s
-// moved; non-temporal stores gained 2 % there and cost the Brusselator, whose
+// Measured (us per step, launches one after the other; one step per launch, the
+// best plan before, tuned, against the default plan here): diffusion 512^3 FP32
+// 189 -> 79 (K 4: 1700 Gcell/s, 1.7 times what the bytes of single steps would
+// allow at 8 TB/s), BF16 121 -> 79 (72 tuned); Brusselator 256^3 FP32 44.3 ->
+// 28.5, BF16 42.3 -> 28.8; pollutant 512x512x128 FP32 218 -> 124; small grids,
+// where a launch is the latency of its chain of loads: diffusion 64^3 6.1 -> 2.2,
+// Brusselator 101x90x77 10.2 -> 4.8.  (A profiler's trace, which runs launches
+// apart, has 85 for diffusion 512^3 and 32 for the Brusselator.)  By counters,
+// of the issue slots for vector instructions (four clocks each, at 2.4 GHz) the
+// FP32 launches fill: diffusion 512^3, K 4, 76 %, moving 1.10 times the fields in
+// and out at 3.5 TB/s; Brusselator, K 2, 60 %, 1.10 times at 4.6 TB/s; pollutant,
+// K 2, 58 %, 1.06 times at 4.5 TB/s.
+// Non-temporal stores gained diffusion 512^3 2 % and cost the Brusselator, whose
 // fields stay in the last cache, 20 %.
 //
 // Point sources: a plane that has any in the tile's rows takes a second copy of
 // the cell code; the others have neither a branch per cell nor its waits (with
 // them, and the wind and the source rows looked up plane by plane, the pollutant
-// took 171 us instead of 131, 256x256x64 37.8 instead of 28.1).
+// took 171 us where it took 131 without, 256x256x64 37.8 and 28.1).
 #pragma once
 
 #include "rd_march_cfg.hpp"

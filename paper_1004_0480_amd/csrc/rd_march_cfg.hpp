@@ -45,10 +45,10 @@ constexpr int march_fields(int pm) {
 
 // Shape i is compiled for this storage and pass model.  More than two steps a
 // launch pay for one field only: with two the arithmetic, repeated in the
-// halos, already takes as long as the memory (Brusselator 256^3 FP32: 28.0 us
+// halos, already takes as long as the memory (Brusselator 256^3 FP32: 28.5 us
 // a step at two steps, 35.2 at four).  For one field FP32 it is the reverse
-// (diffusion 512^3: 116 us at two, 77 at four); two rows per lane never won
-// there.
+// (diffusion 512^3: 104 us at two, 112 at three, 79 at four); two rows per lane
+// never won there.
 constexpr bool march_ok(int storage, int pm, int i) {
     if (i < 0 || i >= kNumMarchCfgs || (storage != ST_F32 && storage != ST_BF16)) return false;
     const int nf = march_fields(pm);
