@@ -109,14 +109,21 @@ def trace_steps(name: str) -> int:
     return 1
 
 
+def traffic_path(name: str, kind: str) -> str:
+    """The PMC summary of a workload and kernel kind.  Summaries are told apart
+    by the kind their names end in; `fmarch_kernel` ends as `march_kernel` does,
+    so the front march's has an ending of its own."""
+    end = "traffic" if kind == "fmarch_kernel" else "pmc"
+    return os.path.join(PROFILES, "%s_%s_%s.json" % (name, kind, end))
+
+
 def measured_traffic(name: str, digest: str, kernel=0):
     """The committed rocprofv3 PMC summary of this workload on the kind of
     kernel the plan runs (its number or name), if it was taken on the current
     kernel sources; else None."""
     kind = kernel if isinstance(kernel, str) else KERNEL_NAMES.get(kernel, "?")
-    path = os.path.join(PROFILES, "%s_%s_pmc.json" % (name, kind))
     try:
-        with open(path) as fh:
+        with open(traffic_path(name, kind)) as fh:
             rec = json.load(fh)
     except (OSError, ValueError):
         return None
@@ -281,7 +288,7 @@ def pmc_summary(args):
            "alg_bytes_per_cell": bpc, "algorithmic_bytes_per_launch_set": alg,
            "traffic_over_algorithmic": (rd_b + wr_b) / alg}
     kind = kind_of(knames[0])
-    out = os.path.join(PROFILES, "%s_%s_pmc.json" % (profile_name(args), kind))
+    out = traffic_path(profile_name(args), kind)
     with open(out, "w") as fh:
         json.dump(rec, fh, indent=1)
     print(json.dumps(rec))

@@ -121,6 +121,24 @@ def test_committed_trace_summary_names_its_command_and_kernel(path):
     assert int(calls) >= 100 and 1.0 < float(avg) < 10000.0
 
 
+def test_front_march_traffic_is_found_and_adds_up():
+    """The headline's kernel has a summary the benchmark reports while the
+    sources are those it was taken on, and its figures follow from its counters."""
+    path = bench.traffic_path("front384", "fmarch_kernel")
+    rec = json.load(open(path))
+    assert bench.measured_traffic("front384", rec["source_digest"], "fmarch_kernel") == rec
+    assert bench.measured_traffic("front384", "0" * 16, "fmarch_kernel") is None
+    assert "rdk::fmarch_kernel" in rec["kernel"] and rec["steps_per_launch"] == 1
+    k, = rec["per_kernel"]
+    moved = (k["fetch_kib_raw"] / rec["copy_fetch_kib_raw"] + k["write_kib_raw"] / rec["copy_write_kib_raw"]) * \
+        bench.COPY_PROBE_BYTES
+    assert rec["hbm_bytes_per_step"] == pytest.approx(moved)
+    cells = int(np.prod(W.DEFAULT_SHAPES["front384"]))
+    assert rec["algorithmic_bytes_per_launch_set"] == bench.alg_bytes_per_cell("front384", "f32", True) * cells
+    assert rec["traffic_over_algorithmic"] == pytest.approx(moved / (24 * cells))
+    assert 0.99 < rec["traffic_over_algorithmic"] < 1.5
+
+
 def test_every_summary_has_a_kind_the_bench_knows():
     assert PMC and TRACES
     for p in PMC + TRACES:
