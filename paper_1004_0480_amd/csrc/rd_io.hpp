@@ -150,12 +150,17 @@ __global__ __launch_bounds__(256) void reduce_final(const double* part, int n, d
 template <int DEPTH, class In, class Out, class Up, class Down>
 __device__ __forceinline__ void convert_rows(const void* src, void* dst, int nx, long long rows, int run, int parts,
                                              int in, int out, Up up, Down down) {
-    const unsigned group = blockIdx.x / unsigned(parts), part = blockIdx.x - group * unsigned(parts);
-    const long long row0 = (long long)group * run;
     const int nx4 = (nx + 3) / 4;
-    const unsigned all = unsigned(min((long long)run, rows - row0)) * unsigned(nx4);
-    const unsigned each = (all + unsigned(parts) - 1) / unsigned(parts);
-    const unsigned first = part * each, units = min(first + each, all);
+    long long row0 = (long long)blockIdx.x * run;
+    unsigned first = 0, units = unsigned(nx4);
+    if (parts == 1) {
+        units *= unsigned(min((long long)run, rows - row0));
+    } else {                                     // (run is 1)
+        const unsigned each = (units + unsigned(parts) - 1) / unsigned(parts);
+        row0 = blockIdx.x / unsigned(parts);
+        first = (blockIdx.x - unsigned(row0) * unsigned(parts)) * each;
+        units = min(first + each, units);
+    }
     const long long end = (rows - 1) * in + (in & 3 ? nx : in);
     for (unsigned u = first + threadIdx.x; u < units; u += 256 * DEPTH) {
         Vec<In, 4> v[DEPTH];

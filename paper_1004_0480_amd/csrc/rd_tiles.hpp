@@ -13,19 +13,9 @@ namespace rdk {
 // chunk, or (zfast: a plan's order 1) the z chunk first.
 struct MarchTile { int x, y, z; };
 RD_TILES_FN MarchTile march_tile(int b, int tiles_x, int tiles_y, int chunks, bool zfast) {
-    MarchTile t;
-    if (zfast) {
-        t.z = b % chunks;
-        b /= chunks;
-        t.x = b % tiles_x;
-        t.y = b / tiles_x;
-    } else {
-        t.x = b % tiles_x;
-        b /= tiles_x;
-        t.y = b % tiles_y;
-        t.z = b / tiles_y;
-    }
-    return t;
+    const int n0 = zfast ? chunks : tiles_x, n1 = zfast ? tiles_x : tiles_y;
+    const int r = b / n0, i0 = b - r * n0, i2 = r / n1, i1 = r - i2 * n1;
+    return zfast ? MarchTile{i1, i2, i0} : MarchTile{i0, i1, i2};
 }
 
 }  // namespace rdk
