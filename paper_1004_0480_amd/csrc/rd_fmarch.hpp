@@ -19,7 +19,7 @@
 // species and lane, which holds exactly its four cells) 369 -> 295; 248x200x180
 // BF16 29; default plans: 384x384x512 FP32 427 -> 371, BF16 381 -> 254, with
 // rounding 295, 248x200x180 FP32 62 -> 42, BF16 65 -> 32, 64^3 26 -> 7.3.  At
-// 384x384x512 FP32 it is bound by memory: 1.98 GB of traffic a step (1.09 times
+// 384x384x512 FP32 it is bound by memory: 1.97 GB of traffic a step (1.09 times
 // the fields: the tiles' halos) at 5.3 TB/s, a third of the issue slots of the
 // vector units filled.  In BF16 it is half of them (1.03 GB at 4 TB/s), with
 // rounding 79 %, 43 % of the instructions for the generator.

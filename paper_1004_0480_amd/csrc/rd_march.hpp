@@ -44,11 +44,11 @@
 // 28.5, BF16 42.3 -> 28.8; pollutant 512x512x128 FP32 218 -> 124; small grids,
 // where a launch is the latency of its chain of loads: diffusion 64^3 6.1 -> 2.2,
 // Brusselator 101x90x77 10.2 -> 4.8.  (A profiler's trace, which runs launches
-// apart, has 85 for diffusion 512^3 and 32 for the Brusselator.)  By counters,
+// apart, has 82 to 86 for diffusion 512^3 and 32 for the Brusselator.)  By counters,
 // of the issue slots for vector instructions (four clocks each, at 2.4 GHz) the
-// FP32 launches fill: diffusion 512^3, K 4, 76 %, moving 1.10 times the fields in
-// and out at 3.5 TB/s; Brusselator, K 2, 60 %, 1.10 times at 4.6 TB/s; pollutant,
-// K 2, 58 %, 1.06 times at 4.5 TB/s.
+// FP32 launches fill: diffusion 512^3, K 4, 76 to 79 %, moving 1.10 times the
+// fields in and out at 3.5 TB/s; Brusselator, K 2, 61 %, 1.10 times at 4.6 TB/s;
+// pollutant, K 2, 58 %, 1.06 times at 4.5 TB/s.
 // Non-temporal stores gained diffusion 512^3 2 % and cost the Brusselator, whose
 // fields stay in the last cache, 20 %.
 //

@@ -14,11 +14,11 @@
 // level, so a level is two planes behind the one below it, and one barrier a
 // plane serves all.  More than two steps do not fit the registers of two fields
 // (185 at two).  What bounds it is vector issue: by counters, at Turing 192^3
-// 73 % of the slots (four clocks an instruction, at 2.4 GHz) by 93 instructions
-// a cell and step, of which about 50 are the cell's and the rest those of rows
+// 73 to 75 % of the slots (four clocks an instruction, at 2.4 GHz) by 93
+// instructions a cell and step, of which about 50 are the cell's and the rest those of rows
 // and planes that only lead to it; 8 waves per CU.  Measured, us a step of Turing
 // FP32, launches one after the other (a workgroup for every CU, where the grid
-// has chunks enough): 192^3 20.7 (in a profiler's trace 22.9), 256^3 42.2, 64^3
+// has chunks enough): 192^3 20.7 (in a profiler's trace 22.5), 256^3 42.2, 64^3
 // 5.6, 128^3 9.6, 130x101x77 8.4 (direct 59.6); single steps at 192^3 23.4.
 #pragma once
 
